@@ -181,8 +181,8 @@ la_status la_sparse_attn_merge(const la_shape* shape, void* o, float* lse, void*
  * of 8, at most 256) each take a range of whole units and a share cut anywhere.  Written:
  *   *P, *U    (host)  the two counts the arrays below are sized by;
  *   tstart    int32 [U + 1] (device): position of unit u's first tile; tstart[U] = T;
- *   ucount    int32 [U]     (device): 64-key tiles of unit u's list union (a unit with 0 still
- *             runs one tile, so it takes max(1, ucount[u]) positions);
+ *   ucount    int32 [U]     (device): 64-key tiles of unit u's list union that some row of it
+ *             sees (a unit with 0 still runs one tile, so it takes max(1, ucount[u]) positions);
  *   dp_start  int32 [P + 1] (device): workgroup l runs the whole units on [dp_start[l],
  *             dp_start[l + 1]) (rounds: its XCD's consecutive units);
  *   sk_start  int32 [P + 1] (device): and its share [sk_start[l], sk_start[l + 1]) of the

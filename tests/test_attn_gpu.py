@@ -316,3 +316,40 @@ def test_attn_schedule_invariants(case):
     la.sparse_attn_fwd(q, k, v, counts, idx, block, ws=ws)
     info = check_schedule(la.plan_schedule(shape, ws), row_tiles=row_tiles_1d(mask, block, Lk))
     say(f"[sched] {label}: {info}")
+
+
+CAUSAL = [
+    # B, H, Lq, Lk, d, block, F, label: frame edges on and off block and 64-key tile edges
+    (1, 2, 512, 1024, 128, 128, 128, "frames are blocks"),
+    (1, 2, 512, 1100, 64, 128, 64, "two frames a block, unaligned chunk"),
+    (1, 3, 700, 1533, 128, 64, 97, "frames cut blocks and tiles"),
+    (1, 1, 333, 800, 64, 128, 1, "one-token frames"),
+    (1, 2, 300, 700, 64, 64, 5000, "one frame longer than the chunk"),
+]
+
+
+@pytest.mark.parametrize("case", CAUSAL, ids=[c[-1] for c in CAUSAL])
+def test_attn_frame_causal_walks_visible_tiles_only(case):
+    # tiles no row of a query block sees are not in the plan; results equal the oracle's
+    B, H, Lq, Lk, d, block, F, label = case
+    say(f"[causal] {label}: B={B} H={H} Lq={Lq} Lk={Lk} d={d} block={block} F={F}")
+    inp = make_clustered(B, H, Lq, Lk, d, block, F)
+    rng = np.random.default_rng(Lq + F)
+    NQ, NK = -(-Lq // block), -(-Lk // block)
+    mask = (rng.uniform(size=(B, H, NQ, NK)) < 0.5).astype(np.uint8)
+    mask[..., (Lk - Lq) // block:] = 1
+    g = to_gpu(inp)
+    counts, idx = la.mask_to_list(torch.from_numpy(mask).cuda(), block, Lq, Lk, d)
+    shape = la.make_shape(B, H, Lq, Lk, d, block, 0, F)
+    ws = torch.empty(la.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    o, lse = la.sparse_attn_fwd(g["q"], g["k"], g["v"], counts, idx, block, frame_tokens=F, want_lse=True, ws=ws)
+    s = la.plan_schedule(shape, ws)
+    o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, block, frame_tokens=F)
+    compare(bf16_tensor_to_f64(o), lse.cpu().numpy().astype(np.float64), o_ref, lse_ref, label)
+    # visible tiles of each query block's own list: those before its last row's last visible key
+    last = np.minimum(Lq, (np.arange(NQ) + 1) * block) - 1
+    lim = np.minimum(Lk, Lk - Lq + (last // F + 1) * F)
+    key0 = np.arange(0, Lk, 64)
+    own = mask[..., key0 // block].astype(np.int64) * (key0[None, :] < lim[:, None])
+    rt = own.sum(-1).reshape(B * H, NQ)
+    check_schedule(s, row_tiles=rt)
