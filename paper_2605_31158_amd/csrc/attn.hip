@@ -24,16 +24,25 @@
 //
 //   phase    group 0                              group 1
 //   A(h)     M(h): P.V of tile h-1, Q.K^T of h    V(h-1): softmax of tile h-1, then issues the
-//                                                 loads of K(h+1) and V(h)
-//   B(h)     V(h): softmax of tile h              M(h): P.V of tile h-1, Q.K^T of tile h, then
-//                                                 waits for its loads
+//                                                 loads of V(h+1)
+//   B(h)     V(h): softmax of tile h, then        M(h): P.V of tile h-1, Q.K^T of tile h
+//            issues the loads of K(h+2)
 //
 // so on every SIMD one wave feeds the matrix pipeline while the other does the softmax
-// arithmetic.  K and V have two LDS stages each: K(h) in stage h & 1 is read in A(h) and B(h);
-// V(h) in stage h & 1 is read in A(h+1) and B(h+1); the loads of K(h+1) and V(h), issued in
-// A(h), overwrite the stages last read in B(h-1).  Only group 1 issues tile loads (asynchronous
-// buffer-to-LDS, 16 bytes per lane); their buffer descriptors end at Lk, so the ragged last
-// block reads zeros past the end.
+// arithmetic.  K and V have three LDS stages each (tile h in stage h % 3).  The stage that K(h+2)
+// overwrites in B(h) was last read in B(h-1), the one that V(h+1) overwrites in A(h) too; what a
+// wave issues in iteration h it waits for at the end of iteration h+1, so the loads have a whole
+// iteration to land.  They are asynchronous buffer-to-LDS loads, 16 bytes per lane, four per wave
+// and tile; their buffer descriptors end at Lk, so the ragged last block reads zeros past the end.
+//
+// What bounds it: a wave issues at most one instruction every four cycles, scalar ones included,
+// so a V phase lasts as long as its instruction count: 111 vector instructions (32 of them
+// exponentials, 8 cycles each) and what the tile's record, masks and loads need.  Records, masks
+// and load addresses are therefore kept to about 40 scalar instructions (150 and a 9th load in
+// four of the waves, with all loads on group 1: 27 % more cycles).  Measured with every block kept
+// (16 heads, 6240 x 43680, d 128): 2059 -> 1861 us (1.20 PFLOP/s; a large bf16 matrix product
+// reaches 1.39 on the same random data and 1.80 on zeros), on zeros 1608 -> 1263 us (1.77
+// PFLOP/s): on real data the kernel is bound by the card's power.
 //
 // Per wave and 64-key tile (d = 128):
 //   S^T (64 keys x 32 queries) = K_tile (64 x d) . Q^T       16 x v_mfma_f32_32x32x16_bf16
@@ -59,7 +68,7 @@ constexpr int QW = 32;          // query rows per wave
 constexpr int QR = 256;         // query rows per unit (workgroup)
 constexpr int kMaxPersist = 256;        // persistent workgroups: one per CU, at most 256
 // flags of a tile record (see TileRef)
-constexpr int kFlFrom0 = 1 << 4, kFlToEnd = 1 << 5, kFlFirst = 1 << 6, kFlLast = 1 << 7, kFlValid = 1 << 8;
+constexpr int kFlFrom0 = 1 << 4, kFlToEnd = 1 << 5, kFlMask = 1 << 6, kFlLast = 1 << 7, kFlValid = 1 << 8;
 // Bits 16..22 of a tile record's flags: keys at the end of the tile that are padding (0..64).
 constexpr int kFlPadShift = 16;
 
@@ -80,18 +89,11 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2v));
 }
 
-// Workgroup barrier that orders LDS accesses (waits for this wave's LDS operations).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Workgroup barrier for a wave with asynchronous tile loads in flight that it does not wait for
-// here: the LDS release fence of lds_barrier would wait for them (they write LDS).  The empty
-// asm statements keep the compiler from moving memory accesses across the barrier; every LDS
-// read of the wave has been consumed by then.
-__device__ __forceinline__ void barrier_keep_loads() {
+// Workgroup barrier for waves with asynchronous tile loads in flight that they do not wait for
+// here (an LDS release fence would wait for them: they write LDS).  The empty asm statements keep
+// the compiler from moving memory accesses across the barrier; every LDS read of the wave has been
+// consumed by then, and no wave writes LDS except by tile loads.
+__device__ __forceinline__ void phase_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -103,94 +105,78 @@ __device__ __forceinline__ void wait_vmem() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | n);   // vmcnt(n), expcnt and lgkmcnt left at their maximum
 }
 
-// LDS layout: K and V tiles of 64 key rows of D bf16, row-major.  K rows are padded to D*2 + 16
-// bytes: the 32 key rows an MFMA operand read touches (16 per LDS cycle) start in distinct
-// 16-byte bank groups.  V rows are not padded; instead the 64-byte chunks of a row are permuted
-// (chunk c of row r is stored at chunk c ^ vswz(r)): a transpose read touches 4 consecutive rows
-// x 64 contiguous bytes per half-wave, and the permutation spreads those four pieces over all 64
-// banks.  Every K operand read is a lane base plus a compile-time offset, every V read one of
-// D/32 lane bases (base ^ 64 dt) plus a compile-time offset.  A tile is written by wave-wide
-// 16-byte-per-lane loads (1 KiB each) of consecutive 16-byte slots; K padding slots read as zero.
+// LDS layout: K and V tiles of 64 key rows of D bf16, row-major and not padded, so that a tile is
+// an even share of four loads for each of four waves.  In a K row the 16-byte slots are permuted
+// (slot c of row r is stored at slot c ^ kswz(r)): an MFMA operand read touches 16 rows per LDS
+// cycle at one c.  In a V row the 64-byte chunks are (chunk c at chunk c ^ vswz(r)): a transpose
+// read touches 4 consecutive rows x 64 contiguous bytes per half-wave.  Both spread over all 64
+// banks.  Every K operand read is one of D/16 lane bases (base ^ 32 ks) plus a compile-time offset,
+// every V read one of D/32 (base ^ 64 dt).
 template <int D>
 struct Tile {
-  static constexpr int KSTRIDE = D * 2 + 16;
-  static constexpr int VSTRIDE = D * 2;
-  static constexpr int KSLOTS = KSTRIDE / 16;          // 16-byte slots per K row
-  static constexpr int VSLOTS = VSTRIDE / 16;
-  static constexpr int KBYTES = KT * KSTRIDE;
-  static constexpr int VBYTES = KT * VSTRIDE;
-  static constexpr int KINST = KT * KSLOTS / 64;       // wave-wide loads per K tile: 4 KPER + 1
-  static constexpr int VINST = KT * VSLOTS / 64;       // per V tile: 4 VPER
-  static constexpr int KPER = KINST / 4;               // per loading wave (wave 0 loads one more)
-  static constexpr int VPER = VINST / 4;
-  static_assert(KINST % 4 == 1 && VINST % 4 == 0, "load split");
+  static constexpr int STRIDE = D * 2;                 // bytes per row
+  static constexpr int SLOTS = STRIDE / 16;            // 16-byte slots per row
+  static constexpr int BYTES = KT * STRIDE;
+  static constexpr int PER = BYTES / 4096;             // 1 KiB loads per loading wave (four load a tile)
+  // slot permutation of K row r: the 16 rows one LDS cycle of an operand read touches lie in
+  // distinct 16-byte bank groups (D = 64: two rows share the 256 bytes of all banks)
+  __device__ static constexpr int kswz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
   // chunk permutation of V row r: rows 4i..4i+3 get four distinct chunks (D = 128: 4 chunks per
   // row) or, with 128-byte rows (D = 64), rows 4i, 4i+2 and 4i+1, 4i+3 get opposite chunks
   __device__ static constexpr int vswz(int r) { return D == 128 ? (r & 3) : ((r >> 1) & 1); }
 };
 
-// Global byte offset (inside a tile of 64 rows) that lane `lane` of load `n` fetches so that it
-// lands at LDS slot 64 n + lane of a padded layout with `slots` slots per row; padding slots get
-// an offset past any buffer (they read as zero).
-template <int D>
-__device__ inline uint32_t slot_offset(int n, int lane, int slots) {
-  const int slot = 64 * n + lane;
-  const int row = slot / slots, chunk = slot % slots;
-  return chunk < D / 8 ? (uint32_t)(row * D * 2 + chunk * 16) : 0x7fffffffu;
+// Global byte offset that lane `lane` of the i-th load of loading wave lw fetches, less the 1024 i
+// of the instruction's immediate: LDS slot 64 i + lane of the wave's quarter of the tile holds
+// slot s ^ kswz(row) of its row (K) or part w of chunk pc ^ vswz(row) (V).
+template <int D, bool V>
+__device__ inline uint32_t slot_offset(int lw, int i, int lane) {
+  using T = Tile<D>;
+  const int slot = 64 * i + lane;
+  const int row = slot / T::SLOTS, sp = slot % T::SLOTS;
+  const int src = V ? (((sp >> 2) ^ T::vswz(row)) << 2 | (sp & 3)) : (sp ^ T::kswz(row));
+  return (uint32_t)(lw * (T::BYTES / 4) + row * T::STRIDE + src * 16 - 1024 * i);
 }
 
-// The same for the V layout: LDS slot 64 n + lane holds part w (16 bytes) of stored chunk pc of
-// row r, i.e. logical chunk pc ^ vswz(r).
+// This wave's quarter of one tile of K or V (base: the tensor): a buffer descriptor that starts at
+// the tile and ends at its head's Lk (rows past Lk read as zero; nrec 0 reads nothing).  The
+// immediate offset of a load counts for both its addresses, so one LDS base (M0) serves all of
+// them.  Written as one asm statement (the loads return nothing to registers): for the builtin the
+// compiler waits for every load in flight before some of the LDS reads, at the loop head, where it
+// cannot tell the stages apart.  The s_nop covers M0 and a descriptor word written just before by
+// a VALU instruction (v_readlane).
 template <int D>
-__device__ inline uint32_t vslot_offset(int n, int lane) {
-  constexpr int SL = D / 8;
-  const int slot = 64 * n + lane;
-  const int row = slot / SL, sp = slot % SL;
-  const int chunk = (sp >> 2) ^ Tile<D>::vswz(row);
-  return (uint32_t)(row * D * 2 + chunk * 64 + (sp & 3) * 16);
+__device__ __forceinline__ void issue_tile(unsigned char* dst, const uint16_t* base, uint64_t off, uint32_t nrec,
+                                           const uint32_t* lane_off) {
+  const uint64_t b = (uint64_t)(uintptr_t)base + off;
+  const u32x4 rsrc = u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, nrec, 0x00020000u};
+  const uint32_t m0 = (uint32_t)(uintptr_t)(LDS_AS unsigned char*)dst;
+  if constexpr (Tile<D>::PER == 4)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                 "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
+                 ::"s"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]), "s"(rsrc)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                 "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
+                 ::"s"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "s"(rsrc)
+                 : "memory");
 }
-
-// Loads of one tile of one matrix by one loading wave: a buffer descriptor that starts at the
-// tile and ends at Lk (rows past Lk read as zero; an invalid tile reads nothing) and the LDS
-// destination.  Load j fills LDS bytes [1024 (lw + 4 j), + 1024) of the tile.
-struct TileLoad {
-  __amdgpu_buffer_rsrc_t rsrc;
-  unsigned char* dst;
-};
-
-template <int D>
-__device__ inline TileLoad tile_load(unsigned char* dst, const uint16_t* base, int key0, int Lk, bool valid) {
-  const uint32_t nrec = valid && key0 < Lk ? (uint32_t)(Lk - key0) * (uint32_t)(D * 2) : 0u;
-  TileLoad t;
-  t.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(base + (size_t)(valid ? key0 : 0) * D), 0, nrec, 0x00020000);
-  t.dst = dst;
-  return t;
-}
-
-template <int NL>
-struct LoadSet {
-  TileLoad t;
-  int lw;
-  const uint32_t* off;      // off[j]: the lane's global offset for load j
-  __device__ __forceinline__ void issue(int j) const { issue_at(lw + 4 * j, off[j]); }
-  // load n of the tile with the lane offset o
-  __device__ __forceinline__ void issue_at(int n, uint32_t o) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(t.rsrc, (LDS_AS void*)(t.dst + 1024 * n), 16, o, 0, 0, 0);
-  }
-};
 
 struct Geom {
   int Lq, Lk, block, NQ, NK, F, chunk0;
   int BH, U;          // heads and units of the plan (bounds for the fields read from it)
 };
 
-// Per-wave constants of the tile loop (klimit, klimit_wave change with the unit).
+// Per-wave constants of the tile loop (klimit changes with the unit).
 struct WaveCtx {
-  int key_lk;                // Lk
   int klimit;                // keys >= klimit are invisible to this lane's query row
-  int klimit_wave;           // smallest klimit of the wave (tiles below it need no mask)
   int kbase, vbase;          // LDS read bases of this lane inside a K / V tile
-  int h;                     // lane / 32
+  int h4;                    // 4 (lane / 32)
   float scale_log2;
 };
 
@@ -208,7 +194,7 @@ __device__ __forceinline__ void qk_tile(const unsigned char* __restrict__ kb, co
   constexpr int AHEAD = 4;
   bf16x8 ka[NS];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) ka[i] = *(const bf16x8*)(kb + kbase + (i & 1) * 32 * T::KSTRIDE + 32 * (i >> 1));
+  for (int i = 0; i < NS; ++i) ka[i] = *(const bf16x8*)(kb + (kbase ^ (32 * (i >> 1))) + (i & 1) * 32 * T::STRIDE);
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -238,9 +224,9 @@ __device__ __forceinline__ void pv_tile(const unsigned char* __restrict__ vb, co
 #pragma unroll
   for (int i = 0; i < NM; ++i) {
     const int s4 = i / DT, dt = i % DT;
-    const unsigned char* vp = vb + (vbase ^ (64 * dt)) + (16 * s4) * T::VSTRIDE;
+    const unsigned char* vp = vb + (vbase ^ (64 * dt)) + (16 * s4) * T::STRIDE;
     const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp));
-    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp + 8 * T::VSTRIDE));
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp + 8 * T::STRIDE));
     const v8i16 a8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     va[i] = __builtin_bit_cast(bf16x8, a8);
   }
@@ -260,22 +246,17 @@ __device__ __forceinline__ void pv_tile(const unsigned char* __restrict__ vb, co
 // (column l%32); the two lanes l and l^32 together hold the row's 64 keys.
 __device__ __forceinline__ void mask_tile(f32x16* sacc, int key0, int fl, const WaveCtx& w) {
   const int pad = (fl >> kFlPadShift) & 127;
-  if (key0 + KT > w.klimit_wave || pad) {
-    const int lim = min(w.klimit, key0 + KT - pad);
+  const int lim = min(w.klimit - key0, KT - pad) - w.h4;
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+  for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = key0 + 32 * kt + 8 * (i >> 2) + 4 * w.h + (i & 3);
-        if (key >= lim) sacc[kt][i] = -INFINITY;
-      }
-  }
+    for (int i = 0; i < 16; ++i)
+      if (32 * kt + 8 * (i >> 2) + (i & 3) >= lim) sacc[kt][i] = -INFINITY;
 }
 
 // P = 2^(S*scale - m) rounded to bf16 into the four B operands of the P.V product; returns the
 // lane's sum of its 32 values (fp32, before rounding).
-__device__ __forceinline__ float softmax_exp(const f32x16* sacc, bf16x8* pb, float m, float scale_log2) {
-  const float m_use = (m == -INFINITY) ? 0.f : m;
+__device__ __forceinline__ float softmax_exp(const f32x16* sacc, bf16x8* pb, float m_use, float scale_log2) {
   float rs0 = 0.f, rs1 = 0.f;
 #pragma unroll
   for (int s4 = 0; s4 < 4; ++s4) {
@@ -295,41 +276,38 @@ __device__ __forceinline__ float softmax_exp(const f32x16* sacc, bf16x8* pb, flo
 
 // Softmax of one tile with a lazily raised running max (base 2).  P is first formed against the
 // current max m_run, which is left alone while every lane's sum of its 32 values stays within
-// 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise, and on the
-// first tile of a piece, the row max of the tile is taken, m_run raised to it, O and l rescaled,
-// and P formed again.  Most tiles thus skip both the row max and the rescale.  A wave that does
-// not own the tile (use false) runs the first pass on stale scores and drops the result.
+// 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise the row max of
+// the tile is taken, m_run raised to it, O and l rescaled, and P formed again.  Most tiles thus skip
+// both the row max and the rescale.  On the first tile of a piece m_run is -inf: the first pass
+// then gives inf or NaN sums, which fail the test too.
 template <int D>
 __device__ __forceinline__ void softmax_tile(f32x16* sacc, bf16x8* pb, f32x16* oacc, float& m_run, float& l_run,
-                                             float scale_log2, bool use) {
+                                             float scale_log2) {
   constexpr int DT = D / 32;
   float rs = softmax_exp(sacc, pb, m_run, scale_log2);
-  const bool redo = use && (m_run == -INFINITY || !(rs <= 256.f));
-  if (__any(redo)) {
-    if (use) {
-      float mx = -INFINITY;
+  if (__builtin_expect(__any(!(rs <= 256.f)), 0)) {
+    float mx = -INFINITY;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[kt][i]);
-      // lanes l and l^32: the swap gives every lane both halves' values
-      const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, mx),
-                                                       __builtin_bit_cast(uint32_t, mx), false, false);
-      mx = fmaxf(__builtin_bit_cast(float, (uint32_t)sw[0]), __builtin_bit_cast(float, (uint32_t)sw[1]));
-      const float mt = mx * scale_log2;
-      if (mt > m_run) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run - mt);   // 0 while m_run is -inf
-        m_run = mt;
-        l_run *= alpha;
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[kt][i]);
+    // lanes l and l^32: the swap gives every lane both halves' values
+    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, mx),
+                                                     __builtin_bit_cast(uint32_t, mx), false, false);
+    mx = fmaxf(__builtin_bit_cast(float, (uint32_t)sw[0]), __builtin_bit_cast(float, (uint32_t)sw[1]));
+    const float mt = mx * scale_log2;
+    if (mt > m_run) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - mt);   // 0 while m_run is -inf
+      m_run = mt;
+      l_run *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-      }
+        for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
     }
-    rs = softmax_exp(sacc, pb, m_run, scale_log2);
+    rs = softmax_exp(sacc, pb, m_run == -INFINITY ? 0.f : m_run, scale_log2);
   }
-  l_run += use ? rs : 0.f;
+  l_run += rs;
 }
 
 // ---------------------------------------------------------------------------
@@ -613,7 +591,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tiles_kernel(const int32_t*
                                                                   int P, bool fold, int32_t* __restrict__ tstart,
                                                                   int32_t* __restrict__ dp_start,
                                                                   int32_t* __restrict__ sk_start, int NK,
-                                                                  int block, int row_tiles, int4* __restrict__ trec) {
+                                                                  int Lk, int F, int chunk0,
+                                                                  const int32_t* __restrict__ qmap, int block,
+                                                                  int row_tiles, int4* __restrict__ trec) {
   __shared__ int sh[kPlanThreads / 64];
   __shared__ int first_tile;
   const int u = blockIdx.x;
@@ -629,6 +609,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tiles_kernel(const int32_t*
   const int nsub = block / KT;
   const int bh = u / row_tiles;
   int4* out = trec + first_tile;
+  // a tile that ends past the first key some row of the unit does not see needs the mask test
+  int maskfrom = Lk;
+  if (F > 0)
+    for (int L = 0; L < QR / block; ++L) {
+      const int qb = qmap[(size_t)u * (QR / block) + L];
+      if (qb >= 0) maskfrom = (int)min((int64_t)maskfrom, (int64_t)chunk0 + ((int64_t)qb * block / F + 1) * F);
+    }
   const int32_t* ul = ulist + (size_t)u * NK * nsub;
   for (int a = tid; a < n; a += kPlanThreads) {
     int key0 = 0, bits = 0;
@@ -642,7 +629,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tiles_kernel(const int32_t*
         bits |= (KT - min(max(kv, 0), KT)) << kFlPadShift;
       }
     }
-    out[a] = int4{key0, bh, u, bits | (a == 0 ? kFlFrom0 : 0) | (a == n - 1 ? kFlToEnd : 0)};
+    if (key0 + KT > maskfrom || (bits >> kFlPadShift)) bits |= kFlMask;
+    out[a] = int4{key0, bh, u, bits | (a == 0 ? kFlFrom0 : 0) | (a == n - 1 ? kFlToEnd | kFlLast : 0)};
   }
 }
 
@@ -654,42 +642,30 @@ struct WgTiles {
   __device__ int at(int t) const { return t < n1 ? a1 + t : a2 + (t - n1); }
 };
 
-// One tile of a workgroup's work (wave-uniform): record x = first key, y = (batch, head),
-// z = unit, w = ownership bits (0..3) | from0 | to_end (the unit's first / last tile), plus
-// first / last (the piece's, i.e. the unit's tiles inside this workgroup's round part or share)
-// and valid.
+// One tile of a workgroup's work (wave-uniform).  Its record: x = first key, y = (batch, head),
+// z = unit, w = ownership bits (0..3) | from0 | to_end and last (the unit's first / last tile) |
+// mask (some key of it may be invisible to some row) | valid | padding; last is also set on the
+// last tile of the workgroup.  fl is 0 past the end.
 struct TileRef {
-  int key0, bh, unit, fl;
-  __device__ bool valid() const { return fl & kFlValid; }
-  __device__ bool owned(int list) const { return (fl >> list) & 1; }
+  int fl, key0;
 };
-
-__device__ inline TileRef make_tile(const int4& e, int t, const WgTiles& g) {
-  TileRef r{0, 0, 0, 0};
-  if (t < g.N) {
-    // the fields are clamped into range, so that even a plan the workspace no longer holds
-    // (overwritten by another call) reads and writes inside q, k, v, o and the workspace
-    r.key0 = min(max(e.x, 0), g.Lk);
-    r.bh = min(max(e.y, 0), g.BH - 1);
-    r.unit = min(max(e.z, 0), g.U - 1);
-    r.fl = e.w | kFlValid | ((e.w & kFlFrom0) || t == 0 || t == g.n1 ? kFlFirst : 0) |
-           ((e.w & kFlToEnd) || t + 1 == g.N ? kFlLast : 0);
-  }
-  return r;
-}
 
 // The record of the workgroup's tile t, read through the constant address space: the records
 // are written by an earlier kernel and never during this one, so the loads can go through the
-// scalar cache (s_load).  t is clamped to the last tile (N > 0); make_tile ignores a record past
-// the end.
+// scalar cache (s_load).  t is clamped to the last tile (N > 0).
 typedef __attribute__((address_space(4))) const int cint32;
 __device__ inline int4 load_tile(const int4* __restrict__ trec, int t, const WgTiles& g) {
   const cint32* r = (const cint32*)(trec + g.at(t < g.N ? t : g.N - 1));
   return int4{r[0], r[1], r[2], r[3]};
 }
 
-__device__ inline TileRef fetch_tile(const int4* __restrict__ trec, int t, const WgTiles& g) {
-  return make_tile(load_tile(trec, t, g), t, g);
+// The fields are clamped into range, so that even a plan the workspace no longer holds
+// (overwritten by another call) reads and writes inside q, k, v, o and the workspace.
+__device__ __forceinline__ TileRef decode_tile(const int4& e, int t, const WgTiles& g) {
+  TileRef r;
+  r.key0 = (int)min((uint32_t)e.x, (uint32_t)g.Lk);
+  r.fl = t < g.N ? e.w | kFlValid | (t + 1 == g.N ? kFlLast : 0) : 0;
+  return r;
 }
 
 // State of one wave's running unit piece.
@@ -700,7 +676,7 @@ struct WaveState {
   bf16x8 pb[4];
   bf16x8 qreg[D / 16];
   float m_run, l_run;
-  bool rows;        // the wave's rows exist
+  int own;          // ownership bit of the wave's list, 0 when the wave's rows do not exist
   bool from0;       // the running piece starts at its unit's first tile
   int r0w;          // first query row of the wave in its (batch, head)
   int bh;
@@ -726,14 +702,15 @@ struct KArgs {
 // Starts a piece of the unit of tile t: zero O, reset the running max and sum, load the wave's
 // Q rows.
 template <int D>
-__device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const TileRef& t, const KArgs& ka) {
+__device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const int4& e, const KArgs& ka) {
   constexpr int KS = D / 16, DT = D / 32;
   const Geom& gm = ka.gm;
-  st.bh = t.bh;
-  const int qb = ka.qmap[(size_t)t.unit * (QR / gm.block) + ka.my_list];
-  st.r0w = qb >= 0 && qb < gm.NQ ? qb * gm.block + ka.r_sub : gm.Lq;
-  st.rows = st.r0w < gm.Lq;
-  st.from0 = t.fl & kFlFrom0;
+  st.bh = (int)min((uint32_t)e.y, (uint32_t)(gm.BH - 1));
+  const int unit = (int)min((uint32_t)e.z, (uint32_t)(gm.U - 1));
+  const int qb = ka.qmap[(size_t)unit * (QR / gm.block) + ka.my_list];
+  st.r0w = __builtin_amdgcn_readfirstlane(qb >= 0 && qb < gm.NQ ? qb * gm.block + ka.r_sub : gm.Lq);
+  st.own = st.r0w < gm.Lq ? 1 << ka.my_list : 0;
+  st.from0 = e.w & kFlFrom0;
   st.m_run = -INFINITY;
   st.l_run = 0.f;
 #pragma unroll
@@ -755,9 +732,7 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
   // when its chunk frame is not later than t's: n < chunk0 + (t / F + 1) F (context keys,
   // n < chunk0, always pass).  One limit per lane replaces per-key frame arithmetic.
   const int64_t lim = gm.F > 0 ? (int64_t)gm.chunk0 + ((int64_t)row / gm.F + 1) * gm.F : (int64_t)gm.Lk;
-  const int64_t limw = gm.F > 0 ? (int64_t)gm.chunk0 + ((int64_t)st.r0w / gm.F + 1) * gm.F : (int64_t)gm.Lk;
   w.klimit = (int)(lim < gm.Lk ? lim : gm.Lk);
-  w.klimit_wave = (int)(limw < gm.Lk ? limw : gm.Lk);
 }
 
 // Ends a piece: the normalised bf16 output (and lse) when the piece is the whole unit, else the
@@ -806,23 +781,27 @@ __device__ __forceinline__ void end_piece(const WaveState<D>& st, bool to_end, c
   __builtin_amdgcn_s_waitcnt(0);
 }
 
-// M phase of tile `cur` (flags prev_fl of the previous tile): P.V of the previous tile, end of
-// its piece, start of cur's piece, Q.K^T of cur.
+// M phase of tile t (cur; prev: tile t - 1): P.V of the previous tile, the change of piece after a
+// last tile, Q.K^T of this one.
 template <int D>
-__device__ __forceinline__ void m_phase(WaveState<D>& st, WaveCtx& w, int prev_fl, const TileRef& cur,
-                                        const unsigned char* kcur, const unsigned char* vprev, const KArgs& ka) {
-  if ((prev_fl & kFlValid) && ((prev_fl >> ka.my_list) & 1) && st.rows) pv_tile<D>(vprev, st.pb, st.oacc, w.vbase);
-  if ((prev_fl & kFlValid) && (prev_fl & kFlLast)) end_piece<D>(st, prev_fl & kFlToEnd, ka);
-  if (cur.valid() && (cur.fl & kFlFirst)) start_piece<D>(st, w, cur, ka);
-  if (cur.valid() && cur.owned(ka.my_list) && st.rows) qk_tile<D>(kcur, st.qreg, st.sacc, w.kbase);
+__device__ __forceinline__ void m_phase(WaveState<D>& st, WaveCtx& w, int prev_fl, int cur_fl, int t,
+                                        const unsigned char* kcur, const unsigned char* vprev,
+                                        const int4* __restrict__ trec, const WgTiles& g, const KArgs& ka) {
+  if (prev_fl & st.own) pv_tile<D>(vprev, st.pb, st.oacc, w.vbase);
+  if (__builtin_expect(prev_fl & kFlLast, 0)) {
+    end_piece<D>(st, prev_fl & kFlToEnd, ka);
+    if (cur_fl) start_piece<D>(st, w, load_tile(trec, t, g), ka);
+  }
+  if (cur_fl & st.own) qk_tile<D>(kcur, st.qreg, st.sacc, w.kbase);
 }
 
-// V phase of tile `cur`: masks, softmax, P.
+// V phase of a tile: masks, softmax, P.
 template <int D>
-__device__ __forceinline__ void v_phase(WaveState<D>& st, const WaveCtx& w, const TileRef& cur, const KArgs& ka) {
-  const bool use = cur.valid() && cur.owned(ka.my_list) && st.rows;
-  if (use) mask_tile(st.sacc, cur.key0, cur.fl, w);
-  softmax_tile<D>(st.sacc, st.pb, st.oacc, st.m_run, st.l_run, w.scale_log2, use);
+__device__ __forceinline__ void v_phase(WaveState<D>& st, const WaveCtx& w, const TileRef& t) {
+  if (t.fl & st.own) {
+    if (__builtin_expect(t.fl & kFlMask, 0)) mask_tile(st.sacc, t.key0, t.fl, w);
+    softmax_tile<D>(st.sacc, st.pb, st.oacc, st.m_run, st.l_run, w.scale_log2);
+  }
 }
 
 template <int D>
@@ -832,10 +811,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int32_t* __restrict__ qmap, uint16_t* __restrict__ o, float* __restrict__ lse, float* __restrict__ part_o,
     float* __restrict__ part_m, float* __restrict__ part_l, Geom gm, int Tcap, float scale_log2) {
   using T = Tile<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char kb0[T::KBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char kb1[T::KBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char vb0[T::VBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char vb1[T::VBYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char kb0[T::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char kb1[T::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char kb2[T::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char vb0[T::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char vb1[T::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char vb2[T::BYTES];
 
   // XCD-aware numbering: hardware places consecutive workgroup ids on consecutive XCDs (round
   // robin over 8); lambda = x PX + c numbers the workgroups of XCD x consecutively, which is
@@ -883,100 +864,79 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     ka.r_off = ka.my_list * 128 + ka.r_sub;
   }
 
-  // lane-constant global offsets of this wave's tile loads (group 1 loads K and V: KPER + 1 and
-  // VPER per wave, the last K load by wave 0 only)
-  uint32_t koff[T::KPER + 1], voff[T::VPER];
-#pragma unroll
-  for (int j = 0; j <= T::KPER; ++j) koff[j] = slot_offset<D>(j < T::KPER ? lw + 4 * j : 4 * T::KPER, lane, T::KSLOTS);
-#pragma unroll
-  for (int j = 0; j < T::VPER; ++j) voff[j] = vslot_offset<D>(lw + 4 * j, lane);
   WaveCtx w;
-  w.key_lk = gm.Lk;
-  w.kbase = c32 * T::KSTRIDE + 16 * h;
+  w.kbase = c32 * T::STRIDE + 16 * (h ^ T::kswz(c32));
   {
     const int vrow = 4 * h + ((lane & 15) >> 2);   // + multiples of 8 rows in the immediates
-    w.vbase = vrow * T::VSTRIDE + 64 * T::vswz(vrow) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    w.vbase = vrow * T::STRIDE + 64 * T::vswz(vrow) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
   }
-  w.h = h;
+  w.h4 = 4 * h;
   w.scale_log2 = scale_log2;
-  w.klimit = gm.Lk;
-  w.klimit_wave = gm.Lk;
 
   WaveState<D> st;
-  st.m_run = -INFINITY;
-  st.l_run = 0.f;
-  st.rows = false;
-  st.from0 = false;
-  st.r0w = 0;
-  st.bh = 0;
-
   const int N = g.N;
-  int prev_fl = 0, prev_key0 = 0;      // the previous tile: flags and first key
-  TileRef cur = fetch_tile(trec, 0, g);
-  TileRef nxt = fetch_tile(trec, 1, g);
 
-  // this (group 1) wave's loads of K(tile tk) into kdst and V(tile tv) into vdst
-  auto issue_loads = [&](unsigned char* kdst, const TileRef& tk, unsigned char* vdst, const TileRef& tv) {
-    const LoadSet<T::KPER> kl{tile_load<D>(kdst, k + (size_t)tk.bh * gm.Lk * D, tk.key0, gm.Lk, tk.valid()), lw, koff};
-    const LoadSet<T::VPER> vl{tile_load<D>(vdst, v + (size_t)tv.bh * gm.Lk * D, tv.key0, gm.Lk, tv.valid()), lw, voff};
-#pragma unroll
-    for (int j = 0; j < T::KPER; ++j) kl.issue(j);
-    if (lw == 0) kl.issue_at(4 * T::KPER, koff[T::KPER]);
-#pragma unroll
-    for (int j = 0; j < T::VPER; ++j) vl.issue(j);
-  };
-  // prologue: K of the first tile
-  if (g1) {
-    const LoadSet<T::KPER> a{tile_load<D>(kb0, k + (size_t)cur.bh * gm.Lk * D, cur.key0, gm.Lk, cur.valid()), lw,
-                             koff};
-#pragma unroll
-    for (int j = 0; j < T::KPER; ++j) a.issue(j);
-    if (lw == 0) a.issue_at(4 * T::KPER, koff[T::KPER]);
-    __builtin_amdgcn_s_waitcnt(0);
-  }
-  lds_barrier();
-
-  // Iteration h (phases A(h), B(h)); K(h) in kb[h & 1], V(h) in vb[h & 1].  Group 1 loads K(h+1)
-  // and V(h) in A(h) and waits for them at the end of B(h).  The record of tile h + 2 is fetched
-  // (scalar load) at the start of each V phase and decoded at its end, so that no scalar load is
-  // outstanding during an M phase (it would force the LDS operand reads there to wait for all
-  // LDS traffic).  Two iterations per trip, so that every buffer is a compile-time choice.
+  // Iteration t (phases A(t), B(t)); tile t lies in stage t % 3.  Group 0 loads K(t+2) in its V
+  // phase B(t), group 1 V(t+1) in its V phase A(t); both wait at the end of B(t) for what they
+  // issued in the iteration before.  The record of the tile to load is fetched (scalar load) at the
+  // start of the V phase and decoded at its end, so that no scalar load is outstanding during an M
+  // phase (it would force the LDS operand reads there to wait for all LDS traffic).  Three
+  // iterations per trip, so that every buffer is a compile-time choice.
   auto run = [&](auto G1) {
     constexpr bool IS_G1 = decltype(G1)::value;
-    TileRef nx2;
-    auto iteration = [&](int hh, unsigned char* kc, unsigned char* kn, unsigned char* vc, unsigned char* vp) {
+    const uint16_t* const src = IS_G1 ? v : k;
+    uint32_t off[T::PER];
+#pragma unroll
+    for (int i = 0; i < T::PER; ++i) off[i] = slot_offset<D, IS_G1>(lw, i, lane);
+    auto issue = [&](unsigned char* dst, const int4& e, const TileRef& r) {
+      const uint32_t bh = min((uint32_t)e.y, (uint32_t)(g.BH - 1));
+      const uint32_t nrec = r.fl ? (uint32_t)(g.Lk - r.key0) * (uint32_t)T::STRIDE : 0u;
+      const uint64_t o64 = (uint64_t)bh * ((uint32_t)g.Lk * (uint32_t)T::STRIDE) + (uint32_t)r.key0 * (uint32_t)T::STRIDE;
+      issue_tile<D>(dst + lw * (T::BYTES / 4), src, o64, nrec, off);
+    };
+    TileRef r0, r1, r2;        // tiles t with t % 3 = 0, 1, 2
+    {
+      const int4 e0 = load_tile(trec, 0, g), e1 = load_tile(trec, 1, g);
+      r0 = decode_tile(e0, 0, g);
+      r1 = decode_tile(e1, 1, g);
+      r2 = TileRef{0, 0};
+      start_piece<D>(st, w, e0, ka);
+      issue(IS_G1 ? vb0 : kb0, e0, r0);
       if constexpr (!IS_G1) {
-        m_phase<D>(st, w, prev_fl, cur, kc, vp, ka);
-        lds_barrier();
-        const int4 raw = load_tile(trec, hh + 2, g);
-        v_phase<D>(st, w, cur, ka);
-        nx2 = make_tile(raw, hh + 2, g);
-        lds_barrier();
-      } else {
-        const int4 raw = load_tile(trec, hh + 2, g);
-        v_phase<D>(st, w, TileRef{prev_key0, 0, 0, prev_fl}, ka);
-        nx2 = make_tile(raw, hh + 2, g);
-        issue_loads(kn, nxt, vc, cur);
-        barrier_keep_loads();
-        m_phase<D>(st, w, prev_fl, cur, kc, vp, ka);
-        __builtin_amdgcn_s_waitcnt(0);
-        lds_barrier();
+        issue(kb1, e1, r1);
+        wait_vmem<T::PER>();
       }
-    };
-    auto advance = [&]() {
-      prev_fl = cur.fl;
-      prev_key0 = cur.key0;
-      cur = nxt;
-      nxt = nx2;
-    };
-    for (int hh = 0;; hh += 2) {
-      iteration(hh, kb0, kb1, vb0, vb1);
-      advance();
-      if (hh + 1 > N) break;
-      iteration(hh + 1, kb1, kb0, vb1, vb0);
-      advance();
-      if (hh + 2 > N) break;
     }
+    phase_barrier();
+    auto iteration = [&](int t, TileRef& rp, TileRef& rc, TileRef& rn, unsigned char* kc, unsigned char* kp,
+                         unsigned char* vp, unsigned char* vn) {
+      if constexpr (!IS_G1) {
+        m_phase<D>(st, w, rp.fl, rc.fl, t, kc, vp, trec, g, ka);
+        phase_barrier();
+        const int4 raw = load_tile(trec, t + 2, g);
+        v_phase<D>(st, w, rc);
+        rp = decode_tile(raw, t + 2, g);
+        issue(kp, raw, rp);
+      } else {
+        const int4 raw = load_tile(trec, t + 1, g);
+        v_phase<D>(st, w, rp);
+        rn = decode_tile(raw, t + 1, g);
+        issue(vn, raw, rn);
+        phase_barrier();
+        m_phase<D>(st, w, rp.fl, rc.fl, t, kc, vp, trec, g, ka);
+      }
+      wait_vmem<T::PER>();
+      phase_barrier();
+    };
+    for (int t = 0;; t += 3) {
+      iteration(t, r2, r0, r1, kb0, kb2, vb2, vb1);
+      if (t + 1 > N) break;
+      iteration(t + 1, r0, r1, r2, kb1, kb0, vb0, vb2);
+      if (t + 2 > N) break;
+      iteration(t + 2, r1, r2, r0, kb2, kb1, vb1, vb0);
+      if (t + 3 > N) break;
+    }
+    wait_vmem<0>();            // no load may still write LDS when the workgroup ends
   };
   if (g1) run(std::true_type{});
   else run(std::false_type{});
@@ -1171,7 +1131,8 @@ hipError_t launch_attn_plan(const Dims& dm, const int32_t* counts, const int32_t
     hipLaunchKernelGGL(plan_sched_kernel, dim3(1), dim3(kPlanThreads), 0, st, w.ucount, U, P, w.tstart, w.dp_start,
                        w.sk_start);
   hipLaunchKernelGGL(plan_tiles_kernel, dim3(U), dim3(kPlanThreads), 0, st, w.ulist, w.ucount, kvalid, U, P, fold,
-                     w.tstart, w.dp_start, w.sk_start, dm.NK, dm.block, row_tiles, w.trec);
+                     w.tstart, w.dp_start, w.sk_start, dm.NK, dm.Lk, dm.frame_tokens, dm.chunk0, w.qmap, dm.block, row_tiles,
+                     w.trec);
   return hipGetLastError();
 }
 

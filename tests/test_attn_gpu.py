@@ -353,3 +353,18 @@ def test_attn_frame_causal_walks_visible_tiles_only(case):
     own = mask[..., key0 // block].astype(np.int64) * (key0[None, :] < lim[:, None])
     rt = own.sum(-1).reshape(B * H, NQ)
     check_schedule(s, row_tiles=rt)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 7])
+def test_attn_few_tiles_per_workgroup(n, d):
+    # n whole or ragged 64-key tiles per workgroup: every phase of the three-stage K/V ring, its
+    # start and its end
+    B, H, Lq = 2, 128, 64
+    Lk = 64 * n - (n % 2) * 9 if n > 1 else 64
+    say(f"[attn] ring: d={d} Lk={Lk}")
+    inp = make_clustered(B, H, Lq, Lk, d, 64, 40 + n)
+    mask = np.ones((B, H, 1, -(-Lk // 64)), np.uint8)
+    o, lse = gpu_attn_on_mask(inp, mask, 64)
+    o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, 64)
+    compare(o, lse, o_ref, lse_ref, f"ring d={d} Lk={Lk}")
