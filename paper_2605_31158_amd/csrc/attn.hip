@@ -40,18 +40,23 @@
 // exponentials, 8 cycles each) and what the tile's record, masks and loads need.  Records, masks
 // and load addresses are therefore kept to about 40 scalar instructions (150 and a 9th load in
 // four of the waves, with all loads on group 1: 27 % more cycles).  Measured with every block kept
-// (16 heads, 6240 x 43680, d 128): 2059 -> 1861 us (1.20 PFLOP/s; a large bf16 matrix product
-// reaches 1.39 on the same random data and 1.80 on zeros), on zeros 1608 -> 1263 us (1.77
-// PFLOP/s): on real data the kernel is bound by the card's power.
+// (16 heads, 6240 x 43680, d 128): 2059 -> 1861 us, on zeros 1608 -> 1263 us (1.77 PFLOP/s): on
+// real data the kernel is bound by the card's power, not by its cycles (a large bf16 matrix product
+// reaches 1.39 PFLOP/s on random data and 1.80 on zeros).
 //
-// Per wave and 64-key tile (d = 128):
-//   S^T (64 keys x 32 queries) = K_tile (64 x d) . Q^T       16 x v_mfma_f32_32x32x16_bf16
+// Per wave and 64-key tile:
+//   S^T (64 keys x 32 queries) = K_tile (64 x d) . Q^T        MFMA, bf16 in, fp32 out
 //   online softmax over keys (fp32, base 2; the running max is only raised when a tile's
 //   max exceeds it by more than 2^8, so most tiles skip the rescale of O)
-//   O^T (d x 32) += V^T (d x 64) . P^T (64 x 32)              16 x v_mfma_f32_32x32x16_bf16
-// S^T is computed transposed so that its accumulator layout (each lane holds 16 keys of one
-// query column) is, 8 values at a time, directly the B operand of the P.V product.  The V^T
-// operand is read with the LDS transpose load ds_read_b64_tr_b16 (two per MFMA).
+//   O^T (d x 32) += V^T (d x 64) . P^T (64 x 32)              MFMA
+// S^T is computed transposed so that its accumulator layout is, 8 values at a time, directly the B
+// operand of the P.V product.  The V^T operand is read with the LDS transpose load
+// ds_read_b64_tr_b16 (two per operand).  The MFMA shape is 16x16x32 for d = 128 and 32x32x16 for
+// d = 64.  On random operands the card sustains 2040 TFLOP/s of the first and 1725 of the second
+// (power), but the first holds up the vector instructions of the other wave more (the softmax of a
+// tile takes 1049 cycles beside it, 718 beside the second, 623 alone).  With d = 128 the power
+// decides: 720P 2128 -> 2031 us, 480P dense 1855 -> 1736 us for the whole attention call; with d = 64
+// a tile has the same softmax for half the products, and 16x16x32 was 2-3 % slower.
 #include <math.h>
 
 #include <type_traits>
@@ -75,13 +80,28 @@ constexpr int kFlPadShift = 16;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+// Shape of the MFMAs for head dimension D (MR x MR x KC) and what follows from it: lane l is row or
+// column l % MR of group l / MR; it holds AR accumulator values, of rows acc_row(i) + 4 (l / MR).
+template <int D>
+struct Mma {
+  static constexpr int MR = D == 128 ? 16 : 32;
+  static constexpr int NG = 64 / MR;         // lane groups
+  static constexpr int KC = 8 * NG;          // contraction depth: 8 values per lane
+  static constexpr int QT = 32 / MR;         // MFMA columns of a wave's 32 query rows
+  static constexpr int AR = MR * MR / 64;
+  typedef typename std::conditional<MR == 16, f32x4, f32x16>::type Acc;
+  __device__ static constexpr int acc_row(int i) { return 8 * (i >> 2) + (i & 3); }
+  __device__ static __forceinline__ Acc mma(bf16x8 a, bf16x8 b, Acc c) {
+    if constexpr (MR == 16)
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+};
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 #define LDS_AS __attribute__((address_space(3)))
-
-__device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
 
 // Two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32.
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
@@ -108,10 +128,10 @@ __device__ __forceinline__ void wait_vmem() {
 // LDS layout: K and V tiles of 64 key rows of D bf16, row-major and not padded, so that a tile is
 // an even share of four loads for each of four waves.  In a K row the 16-byte slots are permuted
 // (slot c of row r is stored at slot c ^ kswz(r)): an MFMA operand read touches 16 rows per LDS
-// cycle at one c.  In a V row the 64-byte chunks are (chunk c at chunk c ^ vswz(r)): a transpose
-// read touches 4 consecutive rows x 64 contiguous bytes per half-wave.  Both spread over all 64
-// banks.  Every K operand read is one of D/16 lane bases (base ^ 32 ks) plus a compile-time offset,
-// every V read one of D/32 (base ^ 64 dt).
+// cycle at one c.  In a V row the chunks of 2 MR bytes are (chunk c at chunk c ^ vswz(r)): a
+// transpose read touches, per half-wave, 8 consecutive rows x 32 bytes (MR = 16) or 4 x 64 (32).
+// Both spread over all 64 banks.  Every K operand read is one of D/KC lane bases (base ^ 16 NG ks)
+// plus a compile-time offset, every V read one of D/MR (base ^ 2 MR dt).
 template <int D>
 struct Tile {
   static constexpr int STRIDE = D * 2;                 // bytes per row
@@ -121,9 +141,9 @@ struct Tile {
   // slot permutation of K row r: the 16 rows one LDS cycle of an operand read touches lie in
   // distinct 16-byte bank groups (D = 64: two rows share the 256 bytes of all banks)
   __device__ static constexpr int kswz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
-  // chunk permutation of V row r: rows 4i..4i+3 get four distinct chunks (D = 128: 4 chunks per
-  // row) or, with 128-byte rows (D = 64), rows 4i, 4i+2 and 4i+1, 4i+3 get opposite chunks
-  __device__ static constexpr int vswz(int r) { return D == 128 ? (r & 3) : ((r >> 1) & 1); }
+  // chunk permutation of V row r: eight 32-byte chunks (D = 128), or two of 64 bytes, with two rows
+  // sharing the 256 bytes of all banks (D = 64)
+  __device__ static constexpr int vswz(int r) { return D == 128 ? (r & 7) : ((r >> 1) & 1); }
 };
 
 // Global byte offset that lane `lane` of the i-th load of loading wave lw fetches, less the 1024 i
@@ -134,7 +154,8 @@ __device__ inline uint32_t slot_offset(int lw, int i, int lane) {
   using T = Tile<D>;
   const int slot = 64 * i + lane;
   const int row = slot / T::SLOTS, sp = slot % T::SLOTS;
-  const int src = V ? (((sp >> 2) ^ T::vswz(row)) << 2 | (sp & 3)) : (sp ^ T::kswz(row));
+  constexpr int CS = Mma<D>::MR / 8;           // slots of a V chunk
+  const int src = V ? ((sp / CS) ^ T::vswz(row)) * CS + sp % CS : (sp ^ T::kswz(row));
   return (uint32_t)(lw * (T::BYTES / 4) + row * T::STRIDE + src * 16 - 1024 * i);
 }
 
@@ -142,8 +163,7 @@ __device__ inline uint32_t slot_offset(int lw, int i, int lane) {
 // the tile and ends at its head's Lk (rows past Lk read as zero; nrec 0 reads nothing).  The
 // immediate offset of a load counts for both its addresses, so one LDS base (M0) serves all of
 // them.  Written as one asm statement (the loads return nothing to registers): for the builtin the
-// compiler waits for every load in flight before some of the LDS reads, at the loop head, where it
-// cannot tell the stages apart.  The s_nop covers M0 and a descriptor word written just before by
+// compiler waits for every load in flight before LDS reads whose stage it cannot tell apart.  The s_nop covers M0 and a descriptor word written just before by
 // a VALU instruction (v_readlane).
 template <int D>
 __device__ __forceinline__ void issue_tile(unsigned char* dst, const uint16_t* base, uint64_t off, uint32_t nrec,
@@ -174,9 +194,9 @@ struct Geom {
 
 // Per-wave constants of the tile loop (klimit changes with the unit).
 struct WaveCtx {
-  int klimit;                // keys >= klimit are invisible to this lane's query row
+  int klimit[2];             // keys >= klimit[qt] are invisible to this lane's query row of column qt
   int kbase, vbase;          // LDS read bases of this lane inside a K / V tile
-  int h4;                    // 4 (lane / 32)
+  int g4;                    // 4 (lane / MR)
   float scale_log2;
 };
 
@@ -184,130 +204,167 @@ struct WaveCtx {
 constexpr int kSgMfma = 0x008;
 constexpr int kSgDsRead = 0x100;
 
-// S^T = K Q^T for one 64-key tile: two 32x32 accumulators (keys 0..31, 32..63).  The K operand
-// reads run four MFMAs ahead of their use, so LDS latency overlaps the matrix pipeline.
+// S^T = K Q^T for one 64-key tile: accumulators [MR keys][MR queries].  The K operand reads run
+// AHEAD operands ahead of their use, so LDS latency overlaps the matrix pipeline.
 template <int D>
-__device__ __forceinline__ void qk_tile(const unsigned char* __restrict__ kb, const bf16x8* qreg, f32x16* sacc,
-                                        int kbase) {
-  using T = Tile<D>;
-  constexpr int NS = 2 * (D / 16);       // MFMAs per tile: 2 key halves x D/16 k-steps
-  constexpr int AHEAD = 4;
-  bf16x8 ka[NS];
+__device__ __forceinline__ void qk_tile(const unsigned char* __restrict__ kb,
+                                        const bf16x8 (*qreg)[Mma<D>::QT],
+                                        typename Mma<D>::Acc (*sacc)[Mma<D>::QT], int kbase) {
+  using X = Mma<D>;
+  constexpr int NT = KT / X::MR;                   // key groups
+  constexpr int NO = NT * (D / X::KC);             // K operands per tile
+  constexpr int AHEAD = X::MR == 16 ? 6 : 4;
+  bf16x8 ka[NO];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) ka[i] = *(const bf16x8*)(kb + (kbase ^ (32 * (i >> 1))) + (i & 1) * 32 * T::STRIDE);
+  for (int i = 0; i < NO; ++i)
+    ka[i] = *(const bf16x8*)(kb + (kbase ^ (16 * X::NG * (i / NT))) + (i % NT) * X::MR * Tile<D>::STRIDE);
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
+  for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sacc[kt][i] = 0.f;
+    for (int qt = 0; qt < X::QT; ++qt)
 #pragma unroll
-  for (int i = 0; i < NS; ++i) sacc[i & 1] = mfma32(ka[i], qreg[i >> 1], sacc[i & 1]);
+      for (int i = 0; i < X::AR; ++i) sacc[kt][qt][i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < NO; ++i)
+#pragma unroll
+    for (int qt = 0; qt < X::QT; ++qt) sacc[i % NT][qt] = X::mma(ka[i], qreg[i / NT][qt], sacc[i % NT][qt]);
   __builtin_amdgcn_sched_group_barrier(kSgDsRead, AHEAD, 0);
 #pragma unroll
-  for (int i = 0; i < NS - AHEAD; ++i) {
-    __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
+  for (int i = 0; i < NO - AHEAD; ++i) {
+    __builtin_amdgcn_sched_group_barrier(kSgMfma, X::QT, 0);
     __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
   }
-  __builtin_amdgcn_sched_group_barrier(kSgMfma, AHEAD, 0);
+  __builtin_amdgcn_sched_group_barrier(kSgMfma, X::QT * AHEAD, 0);
 }
 
-// O^T += V^T P^T for one 64-key tile (P in four bf16 B operands of 16 keys each).  The two
-// transpose reads of each V^T operand run two MFMAs ahead of their use.  Column block dt of the
-// lane's rows sits at vbase ^ (64 dt) (see Tile).
+// O^T += V^T P^T for one 64-key tile (P: B operands [step of KC keys][MR queries]).  Slot e of lane
+// group g of a step's contraction index is key 4 g + e (e < 4) or KC/2 + 4 g + e - 4 of the step,
+// which is how the S accumulators lie; the two transpose reads of a V^T operand follow it.  They
+// run AHEAD operands ahead of their use.
 template <int D>
-__device__ __forceinline__ void pv_tile(const unsigned char* __restrict__ vb, const bf16x8* pb, f32x16* oacc,
-                                        int vbase) {
-  using T = Tile<D>;
-  constexpr int DT = D / 32;
-  constexpr int NM = 4 * DT;             // MFMAs per tile
-  constexpr int AHEAD = 2;
-  bf16x8 va[NM];
+__device__ __forceinline__ void pv_tile(const unsigned char* __restrict__ vb, const bf16x8 (*pb)[Mma<D>::QT],
+                                        typename Mma<D>::Acc (*oacc)[Mma<D>::QT], int vbase) {
+  using X = Mma<D>;
+  constexpr int DT = D / X::MR;
+  constexpr int NO = (KT / X::KC) * DT;            // V^T operands per tile
+  constexpr int AHEAD = X::MR == 16 ? 3 : 2;
+  bf16x8 va[NO];
 #pragma unroll
-  for (int i = 0; i < NM; ++i) {
-    const int s4 = i / DT, dt = i % DT;
-    const unsigned char* vp = vb + (vbase ^ (64 * dt)) + (16 * s4) * T::STRIDE;
+  for (int i = 0; i < NO; ++i) {
+    const unsigned char* vp = vb + (vbase ^ (2 * X::MR * (i % DT))) + (X::KC * (i / DT)) * Tile<D>::STRIDE;
     const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp));
-    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp + 8 * T::STRIDE));
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4i16*)(vp + X::KC / 2 * Tile<D>::STRIDE));
     const v8i16 a8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     va[i] = __builtin_bit_cast(bf16x8, a8);
   }
 #pragma unroll
-  for (int i = 0; i < NM; ++i) oacc[i % DT] = mfma32(va[i], pb[i / DT], oacc[i % DT]);
+  for (int i = 0; i < NO; ++i)
+#pragma unroll
+    for (int qt = 0; qt < X::QT; ++qt) oacc[i % DT][qt] = X::mma(va[i], pb[i / DT][qt], oacc[i % DT][qt]);
   __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2 * AHEAD, 0);
 #pragma unroll
-  for (int i = 0; i < NM - AHEAD; ++i) {
-    __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
+  for (int i = 0; i < NO - AHEAD; ++i) {
+    __builtin_amdgcn_sched_group_barrier(kSgMfma, X::QT, 0);
     __builtin_amdgcn_sched_group_barrier(kSgDsRead, 2, 0);
   }
-  __builtin_amdgcn_sched_group_barrier(kSgMfma, AHEAD, 0);
+  __builtin_amdgcn_sched_group_barrier(kSgMfma, X::QT * AHEAD, 0);
 }
 
 // Masks of one tile (ragged tail, frame-causal pairs, padding at the end of the tile): invisible
-// keys get -inf.  Lane holds keys key0 + 32 kt + 8 (i/4) + 4 (l/32) + i%4 of its query row
-// (column l%32); the two lanes l and l^32 together hold the row's 64 keys.
-__device__ __forceinline__ void mask_tile(f32x16* sacc, int key0, int fl, const WaveCtx& w) {
+// keys get -inf.  Lane holds keys key0 + MR kt + acc_row(i) + 4 (l / MR) of its query rows
+// MR qt + l % MR; the NG lanes of one l % MR together hold a row's 64 keys.
+template <int D>
+__device__ __forceinline__ void mask_tile(typename Mma<D>::Acc (*sacc)[Mma<D>::QT], int key0, int fl,
+                                          const WaveCtx& w) {
+  using X = Mma<D>;
   const int pad = (fl >> kFlPadShift) & 127;
-  const int lim = min(w.klimit - key0, KT - pad) - w.h4;
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
+  for (int qt = 0; qt < X::QT; ++qt) {
+    const int lim = min(w.klimit[qt] - key0, KT - pad) - w.g4;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (32 * kt + 8 * (i >> 2) + (i & 3) >= lim) sacc[kt][i] = -INFINITY;
+    for (int kt = 0; kt < KT / X::MR; ++kt)
+#pragma unroll
+      for (int i = 0; i < X::AR; ++i)
+        if (X::MR * kt + X::acc_row(i) >= lim) sacc[kt][qt][i] = -INFINITY;
+  }
 }
 
-// P = 2^(S*scale - m) rounded to bf16 into the four B operands of the P.V product; returns the
-// lane's sum of its 32 values (fp32, before rounding).
-__device__ __forceinline__ float softmax_exp(const f32x16* sacc, bf16x8* pb, float m_use, float scale_log2) {
+// P = 2^(S*scale - m) of the query column qt rounded to bf16 into the B operands of the P.V
+// product; returns the sum of the lane's values (fp32, before rounding).
+template <int D>
+__device__ __forceinline__ float softmax_exp(const typename Mma<D>::Acc (*sacc)[Mma<D>::QT],
+                                             bf16x8 (*pb)[Mma<D>::QT], int qt, float m_use, float scale_log2) {
+  using X = Mma<D>;
   float rs0 = 0.f, rs1 = 0.f;
 #pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4) {
+  for (int s = 0; s < KT / X::KC; ++s) {
     u32x4 pw;
 #pragma unroll
     for (int j2 = 0; j2 < 4; ++j2) {
-      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[s4 >> 1][8 * (s4 & 1) + 2 * j2], scale_log2, -m_use));
-      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[s4 >> 1][8 * (s4 & 1) + 2 * j2 + 1], scale_log2, -m_use));
+      const int e = 8 * s + 2 * j2;
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[e / X::AR][qt][e % X::AR], scale_log2, -m_use));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[e / X::AR][qt][e % X::AR + 1], scale_log2, -m_use));
       pw[j2] = pack_bf16x2(p0, p1);
       rs0 += p0;
       rs1 += p1;
     }
-    pb[s4] = __builtin_bit_cast(bf16x8, pw);
+    pb[s][qt] = __builtin_bit_cast(bf16x8, pw);
   }
   return rs0 + rs1;
 }
 
-// Softmax of one tile with a lazily raised running max (base 2).  P is first formed against the
-// current max m_run, which is left alone while every lane's sum of its 32 values stays within
-// 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise the row max of
-// the tile is taken, m_run raised to it, O and l rescaled, and P formed again.  Most tiles thus skip
-// both the row max and the rescale.  On the first tile of a piece m_run is -inf: the first pass
-// then gives inf or NaN sums, which fail the test too.
+// Max over the NG lanes that hold a query row's keys.
 template <int D>
-__device__ __forceinline__ void softmax_tile(f32x16* sacc, bf16x8* pb, f32x16* oacc, float& m_run, float& l_run,
-                                             float scale_log2) {
-  constexpr int DT = D / 32;
-  float rs = softmax_exp(sacc, pb, m_run, scale_log2);
-  if (__builtin_expect(__any(!(rs <= 256.f)), 0)) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[kt][i]);
-    // lanes l and l^32: the swap gives every lane both halves' values
-    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, mx),
-                                                     __builtin_bit_cast(uint32_t, mx), false, false);
-    mx = fmaxf(__builtin_bit_cast(float, (uint32_t)sw[0]), __builtin_bit_cast(float, (uint32_t)sw[1]));
-    const float mt = mx * scale_log2;
-    if (mt > m_run) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - mt);   // 0 while m_run is -inf
-      m_run = mt;
-      l_run *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-    }
-    rs = softmax_exp(sacc, pb, m_run == -INFINITY ? 0.f : m_run, scale_log2);
+__device__ __forceinline__ float row_max(float x) {
+  if constexpr (Mma<D>::NG == 4) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x),
+                                                    false, false);
+    x = fmaxf(__builtin_bit_cast(float, (uint32_t)s[0]), __builtin_bit_cast(float, (uint32_t)s[1]));
   }
-  l_run += rs;
+  const auto s = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x),
+                                                  false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)s[0]), __builtin_bit_cast(float, (uint32_t)s[1]));
+}
+
+// Softmax of one tile with a lazily raised running max (base 2).  P is first formed against the
+// current max m_run, which is left alone while every lane's sum of its values of a row stays
+// within 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise the row
+// max of the tile is taken, m_run raised to it, O and l rescaled, and P formed again.  Most tiles
+// thus skip both the row max and the rescale.  On the first tile of a piece m_run is -inf: the first
+// pass then gives inf or NaN sums, which fail the test too.
+template <int D>
+__device__ __forceinline__ void softmax_tile(typename Mma<D>::Acc (*sacc)[Mma<D>::QT], bf16x8 (*pb)[Mma<D>::QT],
+                                             typename Mma<D>::Acc (*oacc)[Mma<D>::QT], float* m_run, float* l_run,
+                                             float scale_log2) {
+  using X = Mma<D>;
+  float rs[X::QT];
+  bool redo = false;
+#pragma unroll
+  for (int qt = 0; qt < X::QT; ++qt) {
+    rs[qt] = softmax_exp<D>(sacc, pb, qt, m_run[qt], scale_log2);
+    redo = redo || !(rs[qt] <= 256.f);
+  }
+  if (__builtin_expect(__any(redo), 0)) {
+#pragma unroll
+    for (int qt = 0; qt < X::QT; ++qt) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < KT / X::MR; ++kt)
+#pragma unroll
+        for (int i = 0; i < X::AR; ++i) mx = fmaxf(mx, sacc[kt][qt][i]);
+      const float mt = row_max<D>(mx) * scale_log2;
+      if (mt > m_run[qt]) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - mt);   // 0 while m_run is -inf
+        m_run[qt] = mt;
+        l_run[qt] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < D / X::MR; ++dt) oacc[dt][qt] *= alpha;
+      }
+      rs[qt] = softmax_exp<D>(sacc, pb, qt, m_run[qt] == -INFINITY ? 0.f : m_run[qt], scale_log2);
+    }
+  }
+#pragma unroll
+  for (int qt = 0; qt < X::QT; ++qt) l_run[qt] += rs[qt];
 }
 
 // ---------------------------------------------------------------------------
@@ -671,11 +728,13 @@ __device__ __forceinline__ TileRef decode_tile(const int4& e, int t, const WgTil
 // State of one wave's running unit piece.
 template <int D>
 struct WaveState {
-  f32x16 oacc[D / 32];
-  f32x16 sacc[2];
-  bf16x8 pb[4];
-  bf16x8 qreg[D / 16];
-  float m_run, l_run;
+  using X = Mma<D>;
+  // [..][qt]: the wave's query rows MR qt .. MR qt + MR - 1
+  typename X::Acc oacc[D / X::MR][X::QT];
+  typename X::Acc sacc[KT / X::MR][X::QT];
+  bf16x8 pb[KT / X::KC][X::QT];
+  bf16x8 qreg[D / X::KC][X::QT];
+  float m_run[X::QT], l_run[X::QT];
   int own;          // ownership bit of the wave's list, 0 when the wave's rows do not exist
   bool from0;       // the running piece starts at its unit's first tile
   int r0w;          // first query row of the wave in its (batch, head)
@@ -696,14 +755,14 @@ struct KArgs {
   int my_list;      // list of the unit (query block) the wave's rows belong to
   int r_sub;        // first row of the wave inside its query block
   int r_off;        // first row of the wave inside the unit: my_list * block + r_sub
-  int c32, h;
+  int c, g;         // lane % MR, lane / MR
 };
 
 // Starts a piece of the unit of tile t: zero O, reset the running max and sum, load the wave's
 // Q rows.
 template <int D>
 __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const int4& e, const KArgs& ka) {
-  constexpr int KS = D / 16, DT = D / 32;
+  using X = Mma<D>;
   const Geom& gm = ka.gm;
   st.bh = (int)min((uint32_t)e.y, (uint32_t)(gm.BH - 1));
   const int unit = (int)min((uint32_t)e.z, (uint32_t)(gm.U - 1));
@@ -711,28 +770,31 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
   st.r0w = __builtin_amdgcn_readfirstlane(qb >= 0 && qb < gm.NQ ? qb * gm.block + ka.r_sub : gm.Lq);
   st.own = st.r0w < gm.Lq ? 1 << ka.my_list : 0;
   st.from0 = e.w & kFlFrom0;
-  st.m_run = -INFINITY;
-  st.l_run = 0.f;
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
+  for (int qt = 0; qt < X::QT; ++qt) {
+    st.m_run[qt] = -INFINITY;
+    st.l_run[qt] = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) st.oacc[dt][i] = 0.f;
-  // Q^T operand (32x32x16 B): lane holds Q[row r0w + l%32][16 ks + 8 (l/32) .. + 7]
-  const int row = st.r0w + ka.c32;
+    for (int dt = 0; dt < D / X::MR; ++dt)
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    u32x4 qw = u32x4{0u, 0u, 0u, 0u};
-    if (row < gm.Lq) qw = *(const u32x4*)(ka.q + ((size_t)st.bh * gm.Lq + row) * D + 16 * ks + 8 * ka.h);
-    st.qreg[ks] = __builtin_bit_cast(bf16x8, qw);
+      for (int i = 0; i < X::AR; ++i) st.oacc[dt][qt][i] = 0.f;
+    // Q^T operand: lane holds Q[row r0w + MR qt + l % MR][KC ks + 8 (l / MR) .. + 7]
+    const int row = st.r0w + X::MR * qt + ka.c;
+#pragma unroll
+    for (int ks = 0; ks < D / X::KC; ++ks) {
+      u32x4 qw = u32x4{0u, 0u, 0u, 0u};
+      if (row < gm.Lq) qw = *(const u32x4*)(ka.q + ((size_t)st.bh * gm.Lq + row) * D + X::KC * ks + 8 * ka.g);
+      st.qreg[ks][qt] = __builtin_bit_cast(bf16x8, qw);
+    }
+    // Key n is visible to query row t when n < Lk and, with frames of F tokens inside the chunk,
+    // when its chunk frame is not later than t's: n < chunk0 + (t / F + 1) F (context keys,
+    // n < chunk0, always pass).  One limit per lane and row replaces per-key frame arithmetic.
+    const int64_t lim = gm.F > 0 ? (int64_t)gm.chunk0 + ((int64_t)row / gm.F + 1) * gm.F : (int64_t)gm.Lk;
+    w.klimit[qt] = (int)(lim < gm.Lk ? lim : gm.Lk);
   }
   // complete the Q loads here: left pending, they would make every later Q.K^T (reached also
   // without a piece start) wait for all vector memory traffic, the tile loads in flight included
   __builtin_amdgcn_s_waitcnt(0);
-  // Key n is visible to query row t when n < Lk and, with frames of F tokens inside the chunk,
-  // when its chunk frame is not later than t's: n < chunk0 + (t / F + 1) F (context keys,
-  // n < chunk0, always pass).  One limit per lane replaces per-key frame arithmetic.
-  const int64_t lim = gm.F > 0 ? (int64_t)gm.chunk0 + ((int64_t)row / gm.F + 1) * gm.F : (int64_t)gm.Lk;
-  w.klimit = (int)(lim < gm.Lk ? lim : gm.Lk);
 }
 
 // Ends a piece: the normalised bf16 output (and lse) when the piece is the whole unit, else the
@@ -742,40 +804,43 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
 // The stores are completed before returning (the tile-load waits count only tile loads).
 template <int D>
 __device__ __forceinline__ void end_piece(const WaveState<D>& st, bool to_end, const KArgs& ka) {
-  constexpr int DT = D / 32;
+  using X = Mma<D>;
   const Geom& gm = ka.gm;
-  const int c32 = ka.c32, h = ka.h;
-  // lane holds O^T[32 dt + 8 (i/4) + 4 (l/32) + i%4][query r0w + l%32]
-  const float l = st.l_run + __shfl_xor(st.l_run, 32);
-  const int qrow = st.r0w + c32;
-  if (qrow >= gm.Lq) {
-  } else if (st.from0 && to_end) {
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
-    uint16_t* orow = ka.o + ((size_t)st.bh * gm.Lq + qrow) * D + 4 * h;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+  for (int qt = 0; qt < X::QT; ++qt) {
+    // lane holds O^T[MR dt + acc_row(i) + 4 g][query r0w + MR qt + l % MR]
+    float l = st.l_run[qt];
+    if constexpr (X::NG == 4) l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    const int rw = X::MR * qt + ka.c, qrow = st.r0w + rw;
+    if (qrow >= gm.Lq) {
+    } else if (st.from0 && to_end) {
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      uint16_t* orow = ka.o + ((size_t)st.bh * gm.Lq + qrow) * D + 4 * ka.g;
 #pragma unroll
-      for (int a4 = 0; a4 < 4; ++a4) {
-        u32x2 ow;
-        ow[0] = pack_bf16x2(st.oacc[dt][4 * a4] * inv, st.oacc[dt][4 * a4 + 1] * inv);
-        ow[1] = pack_bf16x2(st.oacc[dt][4 * a4 + 2] * inv, st.oacc[dt][4 * a4 + 3] * inv);
-        *(u32x2*)(orow + 32 * dt + 8 * a4) = ow;
+      for (int dt = 0; dt < D / X::MR; ++dt) {
+        const typename X::Acc x = st.oacc[dt][qt] * inv;
+#pragma unroll
+        for (int i = 0; i < X::AR; i += 4)
+          *(u32x2*)(orow + X::MR * dt + X::acc_row(i)) = u32x2{pack_bf16x2(x[i], x[i + 1]), pack_bf16x2(x[i + 2], x[i + 3])};
       }
-    if (ka.lse && h == 0)
-      ka.lse[(size_t)st.bh * gm.Lq + qrow] = l > 0.f ? (st.m_run + log2f(l)) * 0.69314718055994531f : -INFINITY;
-  } else {
-    const int slot = 2 * ka.lambda + (st.from0 ? 1 : 0);
-    const size_t prow = (size_t)slot * QR + ka.r_off + c32;
-    float* po = ka.part_o + prow * D + 4 * h;
+      if (ka.lse && ka.g == 0)
+        ka.lse[(size_t)st.bh * gm.Lq + qrow] = l > 0.f ? (st.m_run[qt] + log2f(l)) * 0.69314718055994531f : -INFINITY;
+    } else {
+      const int slot = 2 * ka.lambda + (st.from0 ? 1 : 0);
+      const size_t prow = (size_t)slot * QR + ka.r_off + rw;
+      float* po = ka.part_o + prow * D + 4 * ka.g;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < D / X::MR; ++dt) {
+        const typename X::Acc x = st.oacc[dt][qt];
 #pragma unroll
-      for (int a4 = 0; a4 < 4; ++a4)
-        *(f32x4*)(po + 32 * dt + 8 * a4) =
-            f32x4{st.oacc[dt][4 * a4], st.oacc[dt][4 * a4 + 1], st.oacc[dt][4 * a4 + 2], st.oacc[dt][4 * a4 + 3]};
-    if (h == 0) {
-      ka.part_m[prow] = st.m_run;
-      ka.part_l[prow] = l;
+        for (int i = 0; i < X::AR; i += 4)
+          *(f32x4*)(po + X::MR * dt + X::acc_row(i)) = f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+      }
+      if (ka.g == 0) {
+        ka.part_m[prow] = st.m_run[qt];
+        ka.part_l[prow] = l;
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -799,7 +864,7 @@ __device__ __forceinline__ void m_phase(WaveState<D>& st, WaveCtx& w, int prev_f
 template <int D>
 __device__ __forceinline__ void v_phase(WaveState<D>& st, const WaveCtx& w, const TileRef& t) {
   if (t.fl & st.own) {
-    if (__builtin_expect(t.fl & kFlMask, 0)) mask_tile(st.sacc, t.key0, t.fl, w);
+    if (__builtin_expect(t.fl & kFlMask, 0)) mask_tile<D>(st.sacc, t.key0, t.fl, w);
     softmax_tile<D>(st.sacc, st.pb, st.oacc, st.m_run, st.l_run, w.scale_log2);
   }
 }
@@ -811,12 +876,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int32_t* __restrict__ qmap, uint16_t* __restrict__ o, float* __restrict__ lse, float* __restrict__ part_o,
     float* __restrict__ part_m, float* __restrict__ part_l, Geom gm, int Tcap, float scale_log2) {
   using T = Tile<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char kb0[T::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char kb1[T::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char kb2[T::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char vb0[T::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char vb1[T::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char vb2[T::BYTES];
+  using X = Mma<D>;
+  // stages of K, then of V (one array: the lane bases of the V reads include the offset of the V
+  // stages, so that every stage is within reach of the 16-bit immediates)
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[6 * T::BYTES];
 
   // XCD-aware numbering: hardware places consecutive workgroup ids on consecutive XCDs (round
   // robin over 8); lambda = x PX + c numbers the workgroups of XCD x consecutively, which is
@@ -838,7 +901,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps tile-issue math scalar
   const bool g1 = wave >= 4;                                    // the lagging group
   const int lw = wave & 3;                                      // wave within its group
-  const int c32 = lane & 31, h = lane >> 5;
 
   KArgs ka;
   ka.q = q;
@@ -850,8 +912,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   ka.qmap = qmap;
   ka.gm = gm;
   ka.lambda = lambda;
-  ka.c32 = c32;
-  ka.h = h;
+  ka.c = lane % X::MR;
+  ka.g = lane / X::MR;
   // the two waves of SIMD s (s and s + 4) own the two 32-row halves of one 64-row query block,
   // or (128-row blocks) waves {0, 1, 4, 5} and {2, 3, 6, 7} own the two blocks
   if (gm.block == 64) {
@@ -865,12 +927,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 
   WaveCtx w;
-  w.kbase = c32 * T::STRIDE + 16 * (h ^ T::kswz(c32));
+  w.kbase = ka.c * T::STRIDE + 16 * (ka.g ^ T::kswz(ka.c));
   {
-    const int vrow = 4 * h + ((lane & 15) >> 2);   // + multiples of 8 rows in the immediates
-    w.vbase = vrow * T::STRIDE + 64 * T::vswz(vrow) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    const int vrow = 4 * ka.g + ((lane & 15) >> 2);         // + multiples of KC / 2 rows in the immediates
+    w.vbase = 3 * T::BYTES + vrow * T::STRIDE + 2 * X::MR * T::vswz(vrow) + (X::MR == 32 ? 2 * (lane & 16) : 0) +
+              8 * (lane & 3);
   }
-  w.h4 = 4 * h;
+  w.g4 = 4 * ka.g;
   w.scale_log2 = scale_log2;
 
   WaveState<D> st;
@@ -881,13 +944,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // issued in the iteration before.  The record of the tile to load is fetched (scalar load) at the
   // start of the V phase and decoded at its end, so that no scalar load is outstanding during an M
   // phase (it would force the LDS operand reads there to wait for all LDS traffic).  Three
-  // iterations per trip, so that every buffer is a compile-time choice.
+  // iterations per trip, so that every stage is a compile-time choice.
   auto run = [&](auto G1) {
     constexpr bool IS_G1 = decltype(G1)::value;
     const uint16_t* const src = IS_G1 ? v : k;
     uint32_t off[T::PER];
 #pragma unroll
     for (int i = 0; i < T::PER; ++i) off[i] = slot_offset<D, IS_G1>(lw, i, lane);
+    unsigned char* const s0 = ring;
+    unsigned char* const s1 = ring + T::BYTES;
+    unsigned char* const s2 = ring + 2 * T::BYTES;
+    constexpr int VOFF = 3 * T::BYTES;
     auto issue = [&](unsigned char* dst, const int4& e, const TileRef& r) {
       const uint32_t bh = min((uint32_t)e.y, (uint32_t)(g.BH - 1));
       const uint32_t nrec = r.fl ? (uint32_t)(g.Lk - r.key0) * (uint32_t)T::STRIDE : 0u;
@@ -901,39 +968,39 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       r1 = decode_tile(e1, 1, g);
       r2 = TileRef{0, 0};
       start_piece<D>(st, w, e0, ka);
-      issue(IS_G1 ? vb0 : kb0, e0, r0);
+      issue(IS_G1 ? s0 + VOFF : s0, e0, r0);
       if constexpr (!IS_G1) {
-        issue(kb1, e1, r1);
+        issue(s1, e1, r1);
         wait_vmem<T::PER>();
       }
     }
     phase_barrier();
-    auto iteration = [&](int t, TileRef& rp, TileRef& rc, TileRef& rn, unsigned char* kc, unsigned char* kp,
-                         unsigned char* vp, unsigned char* vn) {
+    auto iteration = [&](int t, TileRef& rp, TileRef& rc, TileRef& rn, unsigned char* sc, unsigned char* sp,
+                         unsigned char* sn) {
       if constexpr (!IS_G1) {
-        m_phase<D>(st, w, rp.fl, rc.fl, t, kc, vp, trec, g, ka);
+        m_phase<D>(st, w, rp.fl, rc.fl, t, sc, sp, trec, g, ka);
         phase_barrier();
         const int4 raw = load_tile(trec, t + 2, g);
         v_phase<D>(st, w, rc);
         rp = decode_tile(raw, t + 2, g);
-        issue(kp, raw, rp);
+        issue(sp, raw, rp);
       } else {
         const int4 raw = load_tile(trec, t + 1, g);
         v_phase<D>(st, w, rp);
         rn = decode_tile(raw, t + 1, g);
-        issue(vn, raw, rn);
+        issue(sn + VOFF, raw, rn);
         phase_barrier();
-        m_phase<D>(st, w, rp.fl, rc.fl, t, kc, vp, trec, g, ka);
+        m_phase<D>(st, w, rp.fl, rc.fl, t, sc, sp, trec, g, ka);
       }
       wait_vmem<T::PER>();
       phase_barrier();
     };
     for (int t = 0;; t += 3) {
-      iteration(t, r2, r0, r1, kb0, kb2, vb2, vb1);
+      iteration(t, r2, r0, r1, s0, s2, s1);
       if (t + 1 > N) break;
-      iteration(t + 1, r0, r1, r2, kb1, kb0, vb0, vb2);
+      iteration(t + 1, r0, r1, r2, s1, s0, s2);
       if (t + 2 > N) break;
-      iteration(t + 2, r1, r2, r0, kb2, kb1, vb1, vb0);
+      iteration(t + 2, r1, r2, r0, s2, s1, s0);
       if (t + 3 > N) break;
     }
     wait_vmem<0>();            // no load may still write LDS when the workgroup ends
