@@ -424,10 +424,10 @@ __device__ inline int block_key_limit(int qb, int Lq, int Lk, int block, int F, 
 // it (block_key_limit).  The frames a query block cannot see are the later part of the chunk, 3/8
 // of it with four frames, and a fully masked tile takes as long as a visible one: 24 heads, 14400
 // queries in four frames, 117 of 563 blocks of 128 kept: 2597 -> 1752 us for the whole call.
-// The grouping key of a query block is the first entry of its list past the text blocks when
-// that entry is historical (below h1), NK otherwise: the smallest kept historical block for an
-// ascending list, as the selection writes them, and read in one or a few loads.  Any other
-// list order only changes the grouping.
+// The grouping key of a query block is its entry h0 (the first past the text blocks of an ascending
+// list, as the selection writes them), or the first entry past the text blocks when entry h0 is
+// none, when that is historical (below h1), NK otherwise.  Any other list order only changes the
+// grouping.
 __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t* __restrict__ counts,
                                                                   const int32_t* __restrict__ idx,
                                                                   const int32_t* __restrict__ kvalid, int NQ, int NK,
@@ -440,7 +440,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   __shared__ int sh[kPlanThreads / 64];
   __shared__ int qsel[4];
   __shared__ int slim[4];             // block_key_limit of the unit's query blocks
-  __shared__ int skey[kMaxGroupNQ];
+  __shared__ __attribute__((aligned(16))) uint64_t skey[kMaxGroupNQ + 2];
+  __shared__ int rank[kMaxGroupNQ];
   const int u = blockIdx.x;
   const int bh = u / row_tiles, g = u % row_tiles;
   const int tid = threadIdx.x;
@@ -453,30 +454,53 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   if (grouped)
     for (int i = tid; i < NQ; i += kPlanThreads) {
       const size_t row = (size_t)bh * NQ + i;
-      const int n = min(max(counts[row], 0), NK);
       const int32_t* lst = idx + row * NK;
+      const int first = lst[min(h0, NK - 1)];      // loaded beside the count, not after it
+      const int n = min(max(counts[row], 0), NK);
       int key = NK;
-      for (int a = 0; a < n; ++a) {
-        const int j = lst[a];
-        if (j >= h0) {
-          key = j < h1 ? j : NK;
-          break;
+      if (n > h0 && first >= h0) {
+        key = first < h1 ? first : NK;
+      } else {
+        for (int a = 0; a < n; ++a) {
+          const int j = lst[a];
+          if (j >= h0) {
+            key = j < h1 ? j : NK;
+            break;
+          }
         }
       }
-      // blocks of one frame first: the length of the visible chunk differs by whole frames (at most
-      // 16384 * 16385 < 2^31)
-      if (F > 0) key += ceil_div(block_key_limit(i, Lq, Lk, block, F, chunk0), block) * (NK + 1);
-      skey[i] = key;
+      // blocks of one frame first: the length of the visible chunk differs by whole frames; then the
+      // key, then the block (NK, the block count of the limit and i are below 2^15, 2^15 and 2^10)
+      const int lim = F > 0 ? ceil_div(block_key_limit(i, Lq, Lk, block, F, chunk0), block) : 0;
+      skey[i] = ((uint64_t)lim << 32) | ((uint64_t)key << 16) | (uint64_t)i;
+      rank[i] = 0;
     }
+  if (grouped && tid < 2) skey[NQ + tid] = ~0ull;      // padding of the pairs read below
   __syncthreads();
   if (grouped) {
-    for (int i = tid; i < NQ; i += kPlanThreads) {
-      const int ki = skey[i];
-      int r = 0;
-      for (int j = 0; j < NQ; ++j) {
-        const int kj = skey[j];
-        r += (kj < ki) || (kj == ki && j < i);
+    // rank of every block among its head's keys, all different; the pairs of keys are counted by
+    // kPlanThreads / (blocks rounded up to waves) threads per block (one thread per block and one
+    // key per LDS read: a longer serial chain)
+    const int rows = (NQ + 63) & ~63, parts = rows < kPlanThreads ? kPlanThreads / rows : 1;
+    const int pairs = (NQ + 1) >> 1, per = (pairs + parts - 1) / parts;
+    const ulonglong2* kp = (const ulonglong2*)skey;
+    for (int e = tid; e < rows * parts; e += kPlanThreads) {
+      const int i = e % rows, p0 = (e / rows) * per, p1 = min(p0 + per, pairs);
+      if (i < NQ) {
+        const uint64_t ki = skey[i];
+        int r = 0;
+#pragma unroll 8
+        for (int j = p0; j < p1; ++j) {
+          const ulonglong2 k2 = kp[j];
+          r += (k2.x < ki) + (k2.y < ki);
+        }
+        if (parts == 1) rank[i] = r;
+        else atomicAdd(&rank[i], r);
       }
+    }
+    __syncthreads();
+    for (int i = tid; i < NQ; i += kPlanThreads) {
+      const int r = rank[i];
       if (r >= g * NL && r < g * NL + NL) qsel[r - g * NL] = i;
     }
   } else if (tid < NL && g * NL + tid < NQ) {
@@ -487,15 +511,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
     qmap[(size_t)u * NL + tid] = qsel[tid];
     slim[tid] = block_key_limit(max(qsel[tid], 0), Lq, Lk, block, F, chunk0);
   }
-  for (int L = 0; L < NL; ++L) {
+  // all lists of the unit at once, kPlanThreads / NL threads each (one after another, every list
+  // cost two more dependent loads; with the ranking above 10.4 -> 9.1 us at 400 units of four lists)
+  {
+    const int tpl = kPlanThreads / NL, L = tid / tpl;
     const int qb = qsel[L];
-    if (qb < 0) continue;
-    const size_t row = (size_t)bh * NQ + qb;
-    const int n = min(max(counts[row], 0), NK);
-    const int32_t* lst = idx + row * NK;
-    for (int i = tid; i < n; i += kPlanThreads) {
-      const int j = lst[i];
-      if ((unsigned)j < (unsigned)NK) atomicOr(&own[j >> 3], (1u << L) << ((j & 7) * 4));
+    if (qb >= 0) {
+      const size_t row = (size_t)bh * NQ + qb;
+      const int n = min(max(counts[row], 0), NK);
+      const int32_t* lst = idx + row * NK;
+      for (int i = tid % tpl; i < n; i += tpl) {
+        const int j = lst[i];
+        if ((unsigned)j < (unsigned)NK) atomicOr(&own[j >> 3], (1u << L) << ((j & 7) * 4));
+      }
     }
   }
   __syncthreads();
@@ -737,6 +765,7 @@ struct WaveState {
   float m_run[X::QT], l_run[X::QT];
   int own;          // ownership bit of the wave's list, 0 when the wave's rows do not exist
   bool from0;       // the running piece starts at its unit's first tile
+  int unit;
   int r0w;          // first query row of the wave in its (batch, head)
   int bh;
 };
@@ -749,6 +778,7 @@ struct KArgs {
   float* part_o;
   float* part_m;
   float* part_l;
+  int32_t* cut;
   const int32_t* qmap;
   Geom gm;
   int lambda;
@@ -765,8 +795,8 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
   using X = Mma<D>;
   const Geom& gm = ka.gm;
   st.bh = (int)min((uint32_t)e.y, (uint32_t)(gm.BH - 1));
-  const int unit = (int)min((uint32_t)e.z, (uint32_t)(gm.U - 1));
-  const int qb = ka.qmap[(size_t)unit * (QR / gm.block) + ka.my_list];
+  st.unit = (int)min((uint32_t)e.z, (uint32_t)(gm.U - 1));
+  const int qb = ka.qmap[(size_t)st.unit * (QR / gm.block) + ka.my_list];
   st.r0w = __builtin_amdgcn_readfirstlane(qb >= 0 && qb < gm.NQ ? qb * gm.block + ka.r_sub : gm.Lq);
   st.own = st.r0w < gm.Lq ? 1 << ka.my_list : 0;
   st.from0 = e.w & kFlFrom0;
@@ -800,12 +830,13 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
 // Ends a piece: the normalised bf16 output (and lse) when the piece is the whole unit, else the
 // fp32 partial (O unnormalised, running max m, sum l) in slot 2 lambda (the first piece of the
 // workgroup's stream-K share, which continues an earlier share) or 2 lambda + 1 (its last,
-// continued by a later share).
+// continued by a later share); cut[slot] names the unit (see CutMap).
 // The stores are completed before returning (the tile-load waits count only tile loads).
 template <int D>
 __device__ __forceinline__ void end_piece(const WaveState<D>& st, bool to_end, const KArgs& ka) {
   using X = Mma<D>;
   const Geom& gm = ka.gm;
+  if (!(st.from0 && to_end) && threadIdx.x == 0) ka.cut[2 * ka.lambda + (st.from0 ? 1 : 0)] = st.unit;
 #pragma unroll
   for (int qt = 0; qt < X::QT; ++qt) {
     // lane holds O^T[MR dt + acc_row(i) + 4 g][query r0w + MR qt + l % MR]
@@ -874,7 +905,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int4* __restrict__ trec, const int32_t* __restrict__ dp_start, const int32_t* __restrict__ sk_start,
     const int32_t* __restrict__ qmap, uint16_t* __restrict__ o, float* __restrict__ lse, float* __restrict__ part_o,
-    float* __restrict__ part_m, float* __restrict__ part_l, Geom gm, int Tcap, float scale_log2) {
+    float* __restrict__ part_m, float* __restrict__ part_l, int32_t* __restrict__ cut, Geom gm, int Tcap,
+    float scale_log2) {
   using T = Tile<D>;
   using X = Mma<D>;
   // stages of K, then of V (one array: the lane bases of the V reads include the offset of the V
@@ -895,6 +927,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   g.Lk = gm.Lk;
   g.BH = gm.BH;
   g.U = gm.U;
+  if (threadIdx.x == 0) cut[2 * lambda] = cut[2 * lambda + 1] = -1;    // no piece in either slot yet
   if (g.N <= 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -909,6 +942,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   ka.part_o = part_o;
   ka.part_m = part_m;
   ka.part_l = part_l;
+  ka.cut = cut;
   ka.qmap = qmap;
   ka.gm = gm;
   ka.lambda = lambda;
@@ -1011,19 +1045,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 // Merges the pieces of units that were split across the stream-K shares of the workgroups:
 // O = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s, over the pieces in share order
-// (deterministic).  Workgroup (lambda, c) handles rows [32 c, 32 c + 32) of the unit that starts
-// inside workgroup lambda's share and continues past it, if there is one (each split unit has
-// exactly one such share).  Units handed out in rounds are never split.
+// (deterministic).  The attention kernel leaves in cut[slot] the unit whose piece a slot holds, -1
+// for none; a unit that starts inside share lambda and continues past it has its first piece in
+// slot 2 lambda + 1 and the others in the slots 2 lambda' of the shares that follow.  Workgroup
+// (lambda, c) merges rows [32 c, 32 c + 32) of that unit, if there is one.  Units handed out in
+// rounds are never split.  Latency bound: with the plan's records and unit tables instead of cut,
+// two more loads in a row (18.7 -> 17.7 us at 400 units, 53 MB of partials).
 constexpr int kCombRows = 32;
 constexpr int kCombThreads = 256;
 
 template <int D>
-__global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(const int32_t* __restrict__ tstart,
-                                                                    const int32_t* __restrict__ ucount,
-                                                                    const int32_t* __restrict__ sk_start,
-                                                                    const int4* __restrict__ trec,
+__global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(const int32_t* __restrict__ cut,
                                                                     const int32_t* __restrict__ qmap, int P, int U,
-                                                                    int Tcap, int row_tiles, int Lq, int block,
+                                                                    int row_tiles, int Lq, int block,
                                                                     const float* __restrict__ part_o,
                                                                     const float* __restrict__ part_m,
                                                                     const float* __restrict__ part_l,
@@ -1034,21 +1068,15 @@ __global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(const int32_
   constexpr int NI = kCombRows / RSTEP;        // rows per thread
   constexpr int BATCH = 4;                     // pieces whose loads are in flight together
   const int lam0 = blockIdx.x;
-  const int b = min(max(sk_start[lam0], 0), Tcap), e = min(max(sk_start[lam0 + 1], 0), Tcap);
-  if (b >= e) return;
-  // unit holding tile e - 1: its record names it (clamped, like every index read from the plan)
-  const int u = min(max(trec[e - 1].z, 0), U - 1);
-  const int ts = tstart[u], te = ts + max(1, ucount[u]);
-  if (ts < b || te <= e) return;
-  // The pieces of the unit, in share order: the last piece of this share (slot 2 lam0 + 1), then
-  // the first piece (slot 2 lambda) of every later non-empty share that starts before the unit
-  // ends.  Their slots are listed in LDS first, so that the loads of several pieces can be in
-  // flight together.
+  const int lam = lam0 + 1 + threadIdx.x;
+  const int piece = lam < P ? cut[2 * lam] : -1;
+  const int u = cut[2 * lam0 + 1];
+  if (u < 0 || u >= U) return;                 // (clamped, like every index read from the workspace)
+  // The pieces of the unit, in share order; their slots are listed in LDS first, so that the loads
+  // of several pieces can be in flight together.
   __shared__ int sh[kCombThreads / 64];
   __shared__ int pslot[kMaxPersist + 1];
-  const int lam = lam0 + 1 + threadIdx.x;
-  const int a = lam < P ? sk_start[lam] : 0, z = lam < P ? sk_start[lam + 1] : 0;
-  const int take = lam < P && a < z && a < te;
+  const int take = piece == u;
   int np;
   const int pos = block_excl_scan_i(take, sh, &np);
   if (take) pslot[1 + pos] = 2 * lam;
@@ -1129,6 +1157,7 @@ struct AttnWs {
   float* part_o;
   float* part_m;
   float* part_l;
+  int32_t* cut;
   size_t bytes;
 };
 
@@ -1160,6 +1189,8 @@ AttnWs attn_ws_layout(const Dims& dm, void* base) {
   w.sk_start = (int32_t*)(b + off);
   off += align256((kMaxPersist + 1) * sizeof(int32_t));
   w.part_o = (float*)(b + off);
+  // slot 0 holds no piece (the first share continues none): its room holds cut [2 kMaxPersist]
+  w.cut = (int32_t*)w.part_o;
   off += align256(slots * QR * dm.d * sizeof(float));
   w.part_m = (float*)(b + off);
   off += align256(slots * QR * sizeof(float));
@@ -1213,11 +1244,11 @@ hipError_t launch_attn_run(const Dims& dm, const void* q, const void* k, const v
   if (dm.d == 128)
     hipLaunchKernelGGL(attn_fwd_kernel<128>, dim3(P), dim3(kThreads), 0, st, (const uint16_t*)q,
                        (const uint16_t*)k, (const uint16_t*)v, w.trec, w.dp_start, w.sk_start, w.qmap,
-                       (uint16_t*)o, lse, w.part_o, w.part_m, w.part_l, gm, Tcap, scale_log2);
+                       (uint16_t*)o, lse, w.part_o, w.part_m, w.part_l, w.cut, gm, Tcap, scale_log2);
   else
     hipLaunchKernelGGL(attn_fwd_kernel<64>, dim3(P), dim3(kThreads), 0, st, (const uint16_t*)q,
                        (const uint16_t*)k, (const uint16_t*)v, w.trec, w.dp_start, w.sk_start, w.qmap,
-                       (uint16_t*)o, lse, w.part_o, w.part_m, w.part_l, gm, Tcap, scale_log2);
+                       (uint16_t*)o, lse, w.part_o, w.part_m, w.part_l, w.cut, gm, Tcap, scale_log2);
   return hipGetLastError();
 }
 
@@ -1226,14 +1257,13 @@ hipError_t launch_attn_merge(const Dims& dm, void* o, float* lse, void* ws, hipS
   const int P = persistent_workgroups();
   AttnWs w = attn_ws_layout(dm, ws);
   const dim3 cgrid(P, QR / kCombRows);
+  const int U = dm.BH * row_tiles;
   if (dm.d == 128)
-    hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(kCombThreads), 0, st, w.tstart, w.ucount, w.sk_start, w.trec,
-                       w.qmap, P, dm.BH * row_tiles, (int)attn_tile_capacity(dm), row_tiles, dm.Lq, dm.block,
-                       w.part_o, w.part_m, w.part_l, (uint16_t*)o, lse);
+    hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, dim3(kCombThreads), 0, st, w.cut, w.qmap, P, U, row_tiles,
+                       dm.Lq, dm.block, w.part_o, w.part_m, w.part_l, (uint16_t*)o, lse);
   else
-    hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(kCombThreads), 0, st, w.tstart, w.ucount, w.sk_start, w.trec,
-                       w.qmap, P, dm.BH * row_tiles, (int)attn_tile_capacity(dm), row_tiles, dm.Lq, dm.block,
-                       w.part_o, w.part_m, w.part_l, (uint16_t*)o, lse);
+    hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, dim3(kCombThreads), 0, st, w.cut, w.qmap, P, U, row_tiles,
+                       dm.Lq, dm.block, w.part_o, w.part_m, w.part_l, (uint16_t*)o, lse);
   return hipGetLastError();
 }
 

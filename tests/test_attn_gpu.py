@@ -368,3 +368,22 @@ def test_attn_few_tiles_per_workgroup(n, d):
     o, lse = gpu_attn_on_mask(inp, mask, 64)
     o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, 64)
     compare(o, lse, o_ref, lse_ref, f"ring d={d} Lk={Lk}")
+
+
+@pytest.mark.parametrize("NQ", [1, 63, 65, 130, 257, 513])
+def test_attn_grouping_covers_every_query_block(NQ):
+    # the planner's ranking of a head's query blocks (several threads per block up to 128 blocks,
+    # pairs of keys, an odd last one): every block in one unit, whatever the lists' first entries
+    B, H, block, d = 1, 2, 64, 64
+    Lq, ctx = 64 * NQ - 5, 640
+    Lk = ctx + Lq
+    say(f"[attn] grouping: NQ={NQ}")
+    inp = make_clustered(B, H, Lq, Lk, d, block, NQ)
+    rng = np.random.default_rng(NQ)
+    NK = -(-Lk // block)
+    mask = np.zeros((B, H, NQ, NK), np.uint8)
+    mask[..., :10] = rng.uniform(size=(B, H, NQ, 10)) < 0.3        # ties, empty rows and all keys
+    mask[..., -1] = rng.uniform(size=(B, H, NQ)) < 0.8
+    o, lse = gpu_attn_on_mask(inp, mask, block)
+    o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, block)
+    compare(o, lse, o_ref, lse_ref, f"grouping NQ={NQ}")
