@@ -2,6 +2,7 @@
 // sizing and kernel launches.  Nothing here allocates device memory.
 #include <math.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "la_internal.h"
@@ -35,6 +36,17 @@ la_status make_dims(const la_shape* s, Dims* o) {
   const int64_t units = (int64_t)o->BH * ceil_div(s->Lq, 256);
   if (units * o->NK * (s->block / 64) >= (int64_t(1) << 31)) return LA_ERR_SHAPE;
   return LA_OK;
+}
+
+int device_cu_count() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  if (dev < kDevices && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 0;
+  if (dev < kDevices) known[dev].store(cus, std::memory_order_relaxed);
+  return cus;
 }
 
 size_t select_ws_bytes(const Dims& dm) {

@@ -1203,10 +1203,8 @@ AttnWs attn_ws_layout(const Dims& dm, void* base) {
 // Persistent workgroups: one per CU of the current device, a multiple of 8 (XCD round robin),
 // at most kMaxPersist (the partial slots of the workspace are sized for that many).
 int persistent_workgroups() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-    cus = 8;
+  int cus = device_cu_count();
+  if (cus < 8) cus = 8;
   const int p = cus < kMaxPersist ? cus : kMaxPersist;
   return p & ~7;
 }

@@ -83,6 +83,10 @@ int mse_blocks(int64_t n, int bf16);
 hipError_t launch_latent_mse(const void* a, const void* b, int64_t n, int bf16, double* out, void* ws,
                              hipStream_t st);
 
+// CUs of the current device, 0 when HIP cannot say.  A constant of the device, asked for once per
+// device: four launches of a step need it.
+int device_cu_count();
+
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace la

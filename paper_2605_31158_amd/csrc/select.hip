@@ -455,10 +455,8 @@ __global__ __launch_bounds__(kThreads) void mask_to_list_kernel(const uint8_t* _
 // slots), at most 32 (the LDS tile) and at least 8 (each workgroup stages the head's pooled
 // queries once), so that no round runs on a fraction of the CUs.
 inline int score_group(const Dims& dm) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
+  int cus = device_cu_count();
+  if (cus < 1) cus = 256;
   const int64_t slots = 3 * (int64_t)cus;
   const int64_t blocks = (int64_t)dm.BH * dm.M;
   const int64_t rounds = (blocks + 32 * slots - 1) / (32 * slots);
