@@ -383,12 +383,7 @@ constexpr int kMaxGroupNQ = 1024;   // heads with more query blocks keep the nat
 
 __device__ inline int block_excl_scan_i(int x, int* sh, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = x;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
+  const int incl = (int)wave_incl_scan((uint32_t)x);
   __syncthreads();
   if (lane == 63) sh[wave] = incl;
   __syncthreads();

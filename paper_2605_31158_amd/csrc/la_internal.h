@@ -89,4 +89,40 @@ int device_cu_count();
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// ---------------------------------------------------------------------------
+// Wave-wide sums and scans with DPP row operations, row broadcasts and the row-pair / half-wave
+// swaps: no LDS round trip.  (With __shfl every step is one or two ds_bpermute, over 100 cycles
+// each in a chain; a scan of the selection's 64-bit weights has twelve of them.)
+
+// x of the lane that `ctrl` names, 0 where there is none or its row is not in row_mask
+template <int ctrl, int row_mask>
+__device__ __forceinline__ uint32_t dpp0(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, row_mask, 0xf, false);
+}
+template <int ctrl, int row_mask>
+__device__ __forceinline__ uint64_t dpp0(uint64_t x) {
+  return ((uint64_t)dpp0<ctrl, row_mask>((uint32_t)(x >> 32)) << 32) | dpp0<ctrl, row_mask>((uint32_t)x);
+}
+
+// Inclusive prefix sum over the 64 lanes (all lanes active), of uint32_t or uint64_t.
+template <typename T>
+__device__ __forceinline__ T wave_incl_scan(T x) {
+  x += dpp0<0x111, 0xf>(x);    // row_shr:1 .. 8: inside the rows of 16 lanes
+  x += dpp0<0x112, 0xf>(x);
+  x += dpp0<0x114, 0xf>(x);
+  x += dpp0<0x118, 0xf>(x);
+  x += dpp0<0x142, 0xa>(x);    // row_bcast:15: rows 0 and 2 into rows 1 and 3
+  x += dpp0<0x143, 0xc>(x);    // row_bcast:31: the first half into the second
+  return x;
+}
+
+__device__ __forceinline__ uint64_t read_lane_u64(uint64_t x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Sum over the 64 lanes, in every lane (uniform).
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) { return read_lane_u64(wave_incl_scan(x), 63); }
+
 }  // namespace la

@@ -190,8 +190,8 @@ __device__ inline uint32_t order_key(float s) {
 // ---------------------------------------------------------------------------
 // wave-level helpers (one wave per query-block row: no workgroup barriers)
 
-// Wave-wide reductions (every lane gets the result) and the inclusive scan, with DPP row
-// operations and the row-pair / half-wave swaps: no LDS round trip.
+// Wave-wide reductions (every lane gets the result), with DPP row operations and the row-pair /
+// half-wave swaps; sums and scans of 64-bit weights are in la_internal.h.
 template <typename Op>
 __device__ inline uint32_t wave_allreduce(uint32_t x, Op op) {
   x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, false));    // quad_perm 1,0,3,2
@@ -238,26 +238,6 @@ __device__ inline uint32_t wave_min_u32(uint32_t x) {
 }
 __device__ inline uint32_t wave_max_u32(uint32_t x) {
   return wave_allreduce(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
-}
-__device__ inline uint64_t wave_sum_u64(uint64_t x) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) x += __shfl_xor(x, off);
-  return x;
-}
-// inclusive prefix sum over the 64 lanes
-__device__ inline uint64_t wave_incl_scan_u64(uint64_t x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint64_t y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  return x;
-}
-__device__ inline uint64_t read_lane_u64(uint64_t x, int lane) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
-  return ((uint64_t)hi << 32) | lo;
 }
 
 // One wave per (head, query block).  Lane l holds candidates m = l + 64 j, j < NPER.
@@ -358,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(const float* __re
         loc += hist[4 * lane + t];
         b4[t] = loc;
       }
-      const uint64_t excl = wave_incl_scan_u64(loc) - loc;
+      const uint64_t excl = wave_incl_scan(loc) - loc;
       int hit = -1;
 #pragma unroll
       for (int t = 3; t >= 0; --t)
@@ -396,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(const float* __re
 #pragma unroll
       for (int j = 0; j < NPER; ++j) {
         const uint64_t wt = (w[j] != 0 && uk[j] == ustar) ? w[j] : 0;
-        const uint64_t incl = wave_incl_scan_u64(wt);
+        const uint64_t incl = wave_incl_scan(wt);
         const bool cross = wt != 0 && base + incl >= target && base + incl - wt < target;
         const unsigned long long bal = __ballot(cross);
         if (bal) {
