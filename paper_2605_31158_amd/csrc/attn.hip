@@ -1043,10 +1043,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // (deterministic).  The attention kernel leaves in cut[slot] the unit whose piece a slot holds, -1
 // for none; a unit that starts inside share lambda and continues past it has its first piece in
 // slot 2 lambda + 1 and the others in the slots 2 lambda' of the shares that follow.  Workgroup
-// (lambda, c) merges rows [32 c, 32 c + 32) of that unit, if there is one.  Units handed out in
+// (lambda, c) merges rows [16 c, 16 c + 16) of that unit, if there is one (32 rows: fewer registers
+// free for loads in flight and half the workgroups: 17.0 instead of 14.8 us).  Units handed out in
 // rounds are never split.  Latency bound: with the plan's records and unit tables instead of cut,
-// two more loads in a row (18.7 -> 17.7 us at 400 units, 53 MB of partials).
-constexpr int kCombRows = 32;
+// two more loads in a row (18.7 instead of 17.7 us at 400 units, 53 MB of partials).
+constexpr int kCombRows = 16;
 constexpr int kCombThreads = 256;
 
 template <int D>
