@@ -1,6 +1,6 @@
 // Block selection on gfx950 (Sec. 3.3: pooled proxies, block relevance scores, retained set).
 //
-// Three launches per call, all on the caller's stream:
+// Three launches per call (two for the smallest, see fold_pool_q), all on the caller's stream:
 //   pool_q        one wave per (head, query block): mean of the block's valid rows
 //                 -> q_bar fp32 [BH, NQ, d] (workspace).  Streaming read, every load of a
 //                 lane in flight at once.
@@ -108,11 +108,13 @@ constexpr int kScoreThreads = 512;   // 8 waves: one pooled block in flight per 
 
 // POOLED: the key means come in as kbar fp32 [BH, NK, D] (pooled by the caller) instead of
 // being pooled here from k bf16 [BH, Lk, D].
-template <int D, int BLOCK, int GB, bool POOLED>
+// POOLQ: qin is q bf16 [BH, Lq, D], pooled here by every workgroup of the head, instead of
+// qbar fp32 [BH, NQ, D] (see fold_pool_q).
+template <int D, int BLOCK, int GB, bool POOLED, bool POOLQ>
 __global__ __launch_bounds__(kScoreThreads) void pool_k_score_kernel(const void* __restrict__ kin,
-                                                                const float* __restrict__ qbar,
-                                                                float* __restrict__ scores, int Lk, int NK, int NQ,
-                                                                int h0, int M, int G, float inv_sqrt_d) {
+                                                                const void* __restrict__ qin,
+                                                                float* __restrict__ scores, int Lq, int Lk, int NK,
+                                                                int NQ, int h0, int M, int G, float inv_sqrt_d) {
   constexpr int LD = D + kPadF;
   __shared__ __attribute__((aligned(16))) float kb[GB][LD];
   __shared__ __attribute__((aligned(16))) float qb[kQChunk][LD];
@@ -125,6 +127,7 @@ __global__ __launch_bounds__(kScoreThreads) void pool_k_score_kernel(const void*
   const float inv_block = 1.0f / (float)BLOCK;
   const uint16_t* __restrict__ k = (const uint16_t*)kin;
   const float* __restrict__ kbar = (const float*)kin;
+  const float* __restrict__ qbar = (const float*)qin;
   for (int g = wave; g < gpad; g += kScoreThreads / 64) {
     if (POOLED) {
       if (lane < D / 4) {
@@ -153,11 +156,28 @@ __global__ __launch_bounds__(kScoreThreads) void pool_k_score_kernel(const void*
   for (int i0 = 0; i0 < NQ; i0 += kQChunk) {
     __syncthreads();                              // kb complete / previous chunk consumed
     const int nrows = min(kQChunk, NQ - i0);
-    for (int e = tid; e < kQChunk * (D / 4); e += kScoreThreads) {
-      const int r = e / (D / 4), c4 = e % (D / 4);
-      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (r < nrows) v = *(const f32x4*)(qbar + ((size_t)bh * NQ + i0 + r) * D + c4 * 4);
-      *(f32x4*)&qb[r][c4 * 4] = v;
+    if constexpr (POOLQ) {
+      const uint16_t* q = (const uint16_t*)qin + (size_t)bh * Lq * D;
+      for (int r = wave; r < ((nrows + 15) & ~15); r += kScoreThreads / 64) {
+        float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float inv = 0.f;
+        if (r < nrows) {
+          const int row0 = (i0 + r) * BLOCK, rows = min(BLOCK, Lq - row0);
+          wave_block_sum<D, BLOCK>(q + (size_t)row0 * D, rows, a);
+          inv = 1.0f / (float)rows;
+        }
+        if (lane < CH) {
+          *(f32x4*)&qb[r][lane * 8] = f32x4{a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv};
+          *(f32x4*)&qb[r][lane * 8 + 4] = f32x4{a[4] * inv, a[5] * inv, a[6] * inv, a[7] * inv};
+        }
+      }
+    } else {
+      for (int e = tid; e < kQChunk * (D / 4); e += kScoreThreads) {
+        const int r = e / (D / 4), c4 = e % (D / 4);
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (r < nrows) v = *(const f32x4*)(qbar + ((size_t)bh * NQ + i0 + r) * D + c4 * 4);
+        *(f32x4*)&qb[r][c4 * 4] = v;
+      }
     }
     __syncthreads();
     for (int t = wave; t < NT; t += kScoreThreads / 64) {
@@ -444,21 +464,41 @@ inline int score_group(const Dims& dm) {
   return (int)(g < 8 ? 8 : g > 32 ? 32 : g);
 }
 
-template <int D, int BLOCK, bool POOLED>
-void launch_score(const Dims& dm, const void* kin, const float* qbar, float* scores, hipStream_t st) {
+// Whether the workgroups that score a head pool its queries themselves (each all of them) instead
+// of a launch of pool_q before.  For the smallest calls, up to eight query blocks read by few
+// workgroups: there the launch costs more than the reads (the selection of 2 heads, 4 query blocks
+// and 12 candidates 9.7 -> 8.5 us, of 8 heads, 8 and 32: 11.2 -> 9.8), 0 to 2 us over eleven shapes up
+// to 256 such reads and a launch less for the host.  Past that the reads add up: even at 720 (12.2
+// and 12.2 us), slower beyond (20 heads, 1 query block, 312 candidates of 128: 42.9 -> 48.9 us).
+inline bool fold_pool_q(const Dims& dm, int G) {
+  return dm.NQ <= 8 && (int64_t)ceil_div(dm.M, G) * dm.BH * dm.NQ <= 256;
+}
+
+template <int D, int BLOCK, bool POOLED, bool POOLQ>
+void launch_score(const Dims& dm, const void* kin, const void* qin, float* scores, int G, hipStream_t st) {
   const float inv_sqrt_d = 1.0f / sqrtf((float)dm.d);
-  // pooled means in: the work is the scoring, so fewer, fuller workgroups (32 blocks when that
-  // still gives one per CU, else 16)
-  const int G = POOLED ? ((int64_t)ceil_div(dm.M, 32) * dm.BH >= 256 ? 32 : 16) : score_group(dm);
-  hipLaunchKernelGGL((pool_k_score_kernel<D, BLOCK, 32, POOLED>), dim3(ceil_div(dm.M, G), dm.BH),
-                     dim3(kScoreThreads), 0, st, kin, qbar, scores, dm.Lk, dm.NK, dm.NQ, dm.h0, dm.M, G, inv_sqrt_d);
+  hipLaunchKernelGGL((pool_k_score_kernel<D, BLOCK, 32, POOLED, POOLQ>), dim3(ceil_div(dm.M, G), dm.BH),
+                     dim3(kScoreThreads), 0, st, kin, qin, scores, dm.Lq, dm.Lk, dm.NK, dm.NQ, dm.h0, dm.M, G,
+                     inv_sqrt_d);
 }
 
 template <int D, int BLOCK>
 void launch_pools(const Dims& dm, const void* q, const void* k, float* qbar, float* scores, hipStream_t st) {
+  const int G = score_group(dm);
+  if (fold_pool_q(dm, G)) {
+    launch_score<D, BLOCK, false, true>(dm, k, q, scores, G, st);
+    return;
+  }
   hipLaunchKernelGGL((pool_q_kernel<D, BLOCK>), dim3(ceil_div(dm.NQ, kThreads / 64), dm.BH), dim3(kThreads), 0,
                      st, (const uint16_t*)q, qbar, dm.Lq, dm.NQ);
-  launch_score<D, BLOCK, false>(dm, k, qbar, scores, st);
+  launch_score<D, BLOCK, false, false>(dm, k, qbar, scores, G, st);
+}
+
+// pooled means in: the work is the scoring, so fewer, fuller workgroups (32 blocks when that
+// still gives one per CU, else 16)
+template <int D>
+void launch_score_pooled(const Dims& dm, const float* kbar, const float* qbar, float* scores, hipStream_t st) {
+  launch_score<D, 64, true, false>(dm, kbar, qbar, scores, (int64_t)ceil_div(dm.M, 32) * dm.BH >= 256 ? 32 : 16, st);
 }
 
 float* scores_ws(const Dims& dm, void* ws) {
@@ -505,8 +545,8 @@ hipError_t launch_select_pooled(const Dims& dm, const float* qbar, const float* 
                                 uint8_t* mask, int32_t* counts, int32_t* idx, void* ws, hipStream_t st) {
   float* scores = scores_ws(dm, ws);
   if (dm.M > 0) {
-    if (dm.d == 128) launch_score<128, 64, true>(dm, kbar, qbar, scores, st);
-    else launch_score<64, 64, true>(dm, kbar, qbar, scores, st);
+    if (dm.d == 128) launch_score_pooled<128>(dm, kbar, qbar, scores, st);
+    else launch_score_pooled<64>(dm, kbar, qbar, scores, st);
   }
   return launch_rows(dm, scores, tau, keep_fixed, mask, counts, idx, st);
 }

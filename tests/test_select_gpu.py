@@ -226,3 +226,31 @@ def test_select_without_mask_output():
     for row in np.ndindex(c.shape):
         np.testing.assert_array_equal(b[row][:c[row]], a[row][:c[row]])
     check_list(mask.cpu().numpy(), c, b)
+
+
+FOLD = [
+    # B*H, NQ, M, block, d: both sides of the rule for pooling the queries where they are scored
+    # (at most 8 query blocks, read by few workgroups), the smallest and the largest of it
+    (1, 1, 1, 64, 64), (2, 8, 31, 64, 128), (1, 9, 31, 64, 128), (8, 4, 64, 64, 64), (9, 4, 64, 64, 64),
+    (2, 7, 20, 128, 64), (3, 3, 17, 128, 128),
+]
+
+
+@pytest.mark.parametrize("case", FOLD, ids=[f"bh{c[0]}_nq{c[1]}_m{c[2]}_b{c[3]}_d{c[4]}" for c in FOLD])
+def test_select_small_calls_equal_the_pooled_path(case):
+    # la_select_blocks gives, bit for bit, what selection from la_pool_blocks' means gives, and the
+    # oracle's mask
+    BH, NQ, M, block, d = case
+    Lq, n_text = NQ * block - 3, 0
+    Lk = M * block + Lq
+    say(f"[select] small: {case}")
+    inp = make_clustered(1, BH, Lq, Lk, d, block, 60 + NQ)
+    g = to_gpu(inp)
+    shape = la.make_shape(1, BH, Lq, Lk, d, block)
+    mask, counts, idx = la.select_blocks(g["q"], g["k"], block, 0.9)
+    qbar, kbar = la.pool_blocks(g["q"], block, "q", shape), la.pool_blocks(g["k"], block, "k", shape)
+    mask2, counts2, _ = la.select_pooled(shape, qbar, kbar, tau=0.9)
+    torch.cuda.synchronize()
+    assert torch.equal(mask, mask2) and torch.equal(counts, counts2)
+    check_selection(mask.cpu().numpy(), O.select_blocks(inp["q"], inp["k"], block, tau=tau32(0.9)))
+    check_list(mask.cpu().numpy(), counts.cpu().numpy(), idx.cpu().numpy())
