@@ -272,15 +272,25 @@ __device__ __forceinline__ void pv_tile(const unsigned char* __restrict__ vb, co
 
 // Masks of one tile (ragged tail, frame-causal pairs, padding at the end of the tile): invisible
 // keys get -inf.  Lane holds keys key0 + MR kt + acc_row(i) + 4 (l / MR) of its query rows
-// MR qt + l % MR; the NG lanes of one l % MR together hold a row's 64 keys.
+// MR qt + l % MR; the NG lanes of one l % MR together hold a row's 64 keys.  The record's flag says
+// that some row of the unit needs a mask; in a unit of several frames most waves do not (without
+// the test the 78-of-1560 case of plan_union_kernel takes 564 instead of 515 us).
 template <int D>
 __device__ __forceinline__ void mask_tile(typename Mma<D>::Acc (*sacc)[Mma<D>::QT], int key0, int fl,
                                           const WaveCtx& w) {
   using X = Mma<D>;
   const int pad = (fl >> kFlPadShift) & 127;
+  int vis[X::QT];                    // visible keys at the front of the tile
+  bool need = false;
 #pragma unroll
   for (int qt = 0; qt < X::QT; ++qt) {
-    const int lim = min(w.klimit[qt] - key0, KT - pad) - w.g4;
+    vis[qt] = min(w.klimit[qt] - key0, KT - pad);
+    need = need || vis[qt] < KT;
+  }
+  if (!__any(need)) return;
+#pragma unroll
+  for (int qt = 0; qt < X::QT; ++qt) {
+    const int lim = vis[qt] - w.g4;
 #pragma unroll
     for (int kt = 0; kt < KT / X::MR; ++kt)
 #pragma unroll
@@ -423,6 +433,16 @@ __device__ inline int block_key_limit(int qb, int Lq, int Lk, int block, int F, 
 // list, as the selection writes them), or the first entry past the text blocks when entry h0 is
 // none, when that is historical (below h1), NK otherwise.  Any other list order only changes the
 // grouping.
+// With frames, the blocks of one frame come first and the key decides inside a frame, unless the
+// lists keep many historical blocks (frames_first below).  A unit of one frame walks no tile of a
+// later one: on average 1 - (frames + 1) / (2 frames) of the chunk's blocks less than all of them.
+// But a unit ordered by the key alone shares historical blocks, at the most NL - 1 of every block's
+// own.  Frames come first where that is the smaller of the two, with a fifth added for partial
+// frames and units, so that a plan walks no more tiles than one ordered by the key that walks the
+// whole chunk.  Measured, whole calls: 16 heads, 6240 queries in four frames, 78 of 1560 historical
+// blocks of 64 kept: 143990 tiles and 735 us by frames, 75891 and 511 us by the key.  24 heads,
+// 14400 queries in four frames, 5 of 450 blocks of 128: 222102 tiles by frames, about 279000 by the
+// key.
 __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t* __restrict__ counts,
                                                                   const int32_t* __restrict__ idx,
                                                                   const int32_t* __restrict__ kvalid, int NQ, int NK,
@@ -446,6 +466,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   for (int i = tid; i < nwords; i += kPlanThreads) own[i] = 0;
   if (tid < 4) qsel[tid] = -1;
   const bool grouped = NQ <= kMaxGroupNQ;
+  int nhist = 0;                      // historical entries of this thread's lists (frames only)
   if (grouped)
     for (int i = tid; i < NQ; i += kPlanThreads) {
       const size_t row = (size_t)bh * NQ + i;
@@ -469,8 +490,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
       const int lim = F > 0 ? ceil_div(block_key_limit(i, Lq, Lk, block, F, chunk0), block) : 0;
       skey[i] = ((uint64_t)lim << 32) | ((uint64_t)key << 16) | (uint64_t)i;
       rank[i] = 0;
+      if (F > 0) {
+        // of an ascending list that keeps the whole chunk, what lies before it, less the text blocks
+        // when it keeps them; of any other list, all entries (more than there may be)
+        const int tail = NK - h1;
+        const bool chunk = tail > 0 && n >= tail && lst[n - tail] == h1;
+        const bool text = n >= h0 && lst[max(h0 - 1, 0)] == h0 - 1;
+        nhist += max(0, n - (chunk ? tail : 0) - (text ? h0 : 0));
+      }
     }
   if (grouped && tid < 2) skey[NQ + tid] = ~0ull;      // padding of the pairs read below
+  if (grouped && F > 0) {
+    int hist;
+    block_excl_scan_i(nhist, sh, &hist);
+    const int64_t frames = ceil_div(Lq, F);
+    const bool frames_first = 6 * (int64_t)(NL - 1) * hist * 2 * frames < 5 * (int64_t)NQ * NQ * (frames - 1);
+    if (!frames_first)
+      for (int i = tid; i < NQ; i += kPlanThreads) skey[i] = (uint32_t)skey[i];
+  }
   __syncthreads();
   if (grouped) {
     // rank of every block among its head's keys, all different; the pairs of keys are counted by

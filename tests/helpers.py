@@ -147,3 +147,56 @@ def check_schedule(s, row_tiles=None):
         per_head = uc.reshape(BH, U // BH).sum(1)
         assert (per_head >= rt.max(1)).all() and (per_head <= rt.sum(1)).all(), "unit tiles vs lists"
     return {"T": T, "R": R, "T_rounds": Tdp, "max_load": int(load.max()), "mean_load": T / P}
+
+
+def unit_tiles(counts, idx, block, Lq, Lk, n_text=0, F=0, kvalid=None, order=None, visible=True):
+    """Tiles of every unit of an attention plan, [B*H, units of a head], from the lists and the rule
+    the planner states: a head's query blocks are ordered, cut into units of 256 rows, and a unit
+    walks the 64-key tiles with a valid key that some listed block of it keeps and sees.
+    order: "key" (first kept historical block, NK for none), "frames" (the chunk frames a block
+    sees, then the key), "natural", or None for the planner's choice between them.
+    visible=False: tiles no row sees are walked too."""
+    B, H, NQ = counts.shape
+    NK = idx.shape[-1]
+    NL, nsub = 256 // block, block // 64
+    h0 = -(-n_text // block)
+    h1 = max(h0, (Lk - Lq) // block)
+    valid = np.minimum(block, Lk - block * np.arange(NK))
+    if kvalid is not None:
+        valid = np.minimum(valid, np.clip(kvalid, 0, block))
+    sub = np.arange(nsub)
+    exists = 64 * sub[None, :] < valid[:, None]                                  # [NK, nsub]
+    key0 = block * np.arange(NK)[:, None] + 64 * sub[None, :]
+    last = np.minimum(Lq, block * (np.arange(NQ) + 1)) - 1
+    lim = np.minimum(Lk, Lk - Lq + (last // F + 1) * F) if F > 0 else np.full(NQ, Lk)
+    seen = key0[None] < (lim[:, None, None] if visible else Lk)                  # [NQ, NK, nsub]
+    out = np.zeros((B * H, -(-NQ // NL)), np.int64)
+    for bh in range(B * H):
+        cnt = np.clip(counts.reshape(-1, NQ)[bh], 0, NK)
+        keep = np.zeros((NQ, NK), bool)
+        key = np.full(NQ, NK)
+        hist = 0
+        for i in range(NQ):
+            lst = idx.reshape(-1, NQ, NK)[bh, i]
+            n = int(cnt[i])
+            ent = lst[:n][(lst[:n] >= 0) & (lst[:n] < NK)]
+            keep[i, ent] = True
+            past = lst[h0] if n > h0 and lst[h0] >= h0 else next((j for j in lst[:n] if j >= h0), NK)
+            key[i] = past if past < h1 else NK
+            tail = NK - h1
+            chunk = tail > 0 and n >= tail and lst[min(n - tail, NK - 1)] == h1
+            text = h0 > 0 and n >= h0 and lst[h0 - 1] == h0 - 1
+            hist += max(0, n - (tail if chunk else 0) - (h0 if text else 0))
+        how = order
+        if how is None and NQ > 1024:
+            how = "natural"
+        elif how is None:
+            frames = -(-Lq // F) if F > 0 else 1
+            how = "frames" if 12 * (NL - 1) * hist * frames < 5 * NQ * NQ * (frames - 1) else "key"
+        nat = np.arange(NQ)
+        rank = {"key": np.lexsort((nat, key)), "frames": np.lexsort((nat, key, -(-lim // block))),
+                "natural": nat}[how]
+        tiles = keep[:, :, None] & exists[None] & seen
+        for g in range(out.shape[1]):
+            out[bh, g] = tiles[rank[g * NL:(g + 1) * NL]].any(0).sum()
+    return out

@@ -12,7 +12,7 @@ from oracle import la_oracle as O
 from paper_2605_31158_amd import la
 from paper_2605_31158_amd.workloads import WORKLOADS, CONFIG_ORDER, make_inputs, make_clustered
 from helpers import (say, tau32, to_gpu, check_list, check_selection, check_schedule, assert_attn_close,
-                     bf16_tensor_to_f64)
+                     bf16_tensor_to_f64, unit_tiles)
 
 pytestmark = pytest.mark.gpu
 
@@ -387,3 +387,50 @@ def test_attn_grouping_covers_every_query_block(NQ):
     o, lse = gpu_attn_on_mask(inp, mask, block)
     o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, block)
     compare(o, lse, o_ref, lse_ref, f"grouping NQ={NQ}")
+
+
+ORDER = [
+    # query blocks, frames, historical blocks a block keeps, block, d, keep the text, label
+    (16, 4, 40, 64, 64, True, "many historical blocks"),
+    (16, 4, 1, 64, 64, True, "one historical block"),
+    (12, 3, 24, 128, 128, True, "many, blocks of 128"),
+    (12, 6, 1, 128, 64, True, "one, blocks of 128"),
+    (16, 4, 40, 64, 64, False, "many, lists without the text"),
+]
+
+
+@pytest.mark.parametrize("case", ORDER, ids=[c[-1] for c in ORDER])
+def test_attn_frame_causal_order_of_query_blocks(case):
+    # blocks of the same slot of every frame keep the same historical blocks: sharing them saves more
+    # tiles than the frames a block does not see when there are many, fewer when there are few.  The
+    # plan takes the order its rule says, and never walks more than the key's order with every tile
+    NQ, frames, keep, block, d, text, label = case
+    H, n_text = 2, 70
+    h0 = -(-n_text // block)
+    slots = NQ // frames
+    M = keep * slots
+    Lq = NQ * block
+    Lk = (h0 + M) * block + Lq
+    F = Lq // frames
+    say(f"[causal] order: {label}: Lq={Lq} Lk={Lk} d={d} block={block} F={F}")
+    inp = make_clustered(1, H, Lq, Lk, d, block, NQ + keep)
+    mask = np.zeros((1, H, NQ, h0 + M + NQ), np.uint8)
+    mask[..., :h0] = text
+    mask[..., h0 + M:] = 1
+    for i in range(NQ):
+        mask[:, :, i, h0 + (i % slots) * keep:h0 + (i % slots + 1) * keep] = 1
+    g = to_gpu(inp)
+    counts, idx = la.mask_to_list(torch.from_numpy(mask).cuda(), block, Lq, Lk, d)
+    shape = la.make_shape(1, H, Lq, Lk, d, block, n_text, F)
+    ws = torch.empty(la.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    o, lse = la.sparse_attn_fwd(g["q"], g["k"], g["v"], counts, idx, block, n_text=n_text, frame_tokens=F,
+                                want_lse=True, ws=ws)
+    s = la.plan_schedule(shape, ws)
+    o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, block, frame_tokens=F)
+    compare(bf16_tensor_to_f64(o), lse.cpu().numpy().astype(np.float64), o_ref, lse_ref, label)
+    lists = (counts.cpu().numpy(), idx.cpu().numpy(), block, Lq, Lk, n_text, F)
+    np.testing.assert_array_equal(s["ucount"], unit_tiles(*lists).reshape(-1))
+    total = int(s["ucount"].sum())
+    by_key, by_frame = (int(unit_tiles(*lists, order=x).sum()) for x in ("key", "frames"))
+    assert total <= int(unit_tiles(*lists, order="key", visible=False).sum())
+    assert total == (by_key if keep > 1 else by_frame) == min(by_key, by_frame), (total, by_key, by_frame)
