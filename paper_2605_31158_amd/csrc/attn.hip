@@ -163,8 +163,9 @@ __device__ inline uint32_t slot_offset(int lw, int i, int lane) {
 // the tile and ends at its head's Lk (rows past Lk read as zero; nrec 0 reads nothing).  The
 // immediate offset of a load counts for both its addresses, so one LDS base (M0) serves all of
 // them.  Written as one asm statement (the loads return nothing to registers): for the builtin the
-// compiler waits for every load in flight before LDS reads whose stage it cannot tell apart.  The s_nop covers M0 and a descriptor word written just before by
-// a VALU instruction (v_readlane).
+// compiler waits for every load in flight before LDS reads whose stage it cannot tell apart.  M0 is
+// an operand, so that the compiler writes it and knows what it holds.  The s_nop covers M0 and a
+// descriptor word written just before by a VALU instruction (v_readlane).
 template <int D>
 __device__ __forceinline__ void issue_tile(unsigned char* dst, const uint16_t* base, uint64_t off, uint32_t nrec,
                                            const uint32_t* lane_off) {
@@ -172,18 +173,18 @@ __device__ __forceinline__ void issue_tile(unsigned char* dst, const uint16_t* b
   const u32x4 rsrc = u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, nrec, 0x00020000u};
   const uint32_t m0 = (uint32_t)(uintptr_t)(LDS_AS unsigned char*)dst;
   if constexpr (Tile<D>::PER == 4)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+    asm volatile("s_nop 4\n\t"
                  "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
                  "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
                  "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
                  "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
-                 ::"s"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]), "s"(rsrc)
+                 ::"{m0}"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]), "s"(rsrc)
                  : "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+    asm volatile("s_nop 4\n\t"
                  "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
                  "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
-                 ::"s"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "s"(rsrc)
+                 ::"{m0}"(m0), "v"(lane_off[0]), "v"(lane_off[1]), "s"(rsrc)
                  : "memory");
 }
 

@@ -167,3 +167,20 @@ def test_binding_refuses_cpu_tensors():
     with pytest.raises(TypeError):
         la.sparse_attn_fwd(q, q, q, torch.zeros(1, 1, 1, dtype=torch.int32),
                            torch.zeros(1, 1, 1, 1, dtype=torch.int32), 64)
+
+
+def test_asm_statements_take_m0_as_an_operand():
+    # the compiler keeps M0 across an asm statement that does not name it: one that uses M0 (a load to
+    # LDS) gets it as an operand, and none writes it in its own text
+    csrc = os.path.join(ROOT, "paper_2605_31158_amd", "csrc")
+    statements = []
+    for fn in sorted(os.listdir(csrc)):
+        if fn.endswith((".hip", ".h")):
+            text = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, fn)).read())
+            statements += re.findall(r"\basm\s+volatile\s*\((.*?)\);", text, flags=re.S)
+    loads = [s for s in statements if re.search(r"\blds\b", s)]
+    assert len(loads) == 2
+    for s in loads:
+        assert '"{m0}"(' in s, s
+    for s in statements:
+        assert not re.search(r"s_\w+ m0\b", s), s
