@@ -19,10 +19,11 @@ Before the W warm-up steps the step is repeated for --clock-warmup-ms of wall ti
 default, reported as clock_warmup): the GPU's clock ramps up over the first milliseconds of work,
 and without this the timed steps of the short workloads would partly run before it has.
 
-value = kept-block TFLOP/s of the whole step (kept FLOPs / step time).  The line also
-carries the per-kernel split, the dense baseline (same attention kernel, every block
-kept), the roofline of the attention kernel (la_sparse_attn_run launches exactly that one
-kernel, so its event time is the kernel's launch duration) and the fp64 oracle's CPU rate.
+value = kept-block TFLOP/s of the whole step (kept FLOPs / step time; with frame-causal chunks only
+the keys a row sees count).  The line also carries the per-kernel split, the dense baseline (same
+attention kernel, every block kept), the roofline of the attention kernel (la_sparse_attn_run
+launches exactly that one kernel, so its event time is the kernel's launch duration) and the fp64
+oracle's CPU rate.
 """
 from __future__ import annotations
 
@@ -147,14 +148,19 @@ def stage_times(stages, stream, K: int):
     return np.array([[ev[i][j].elapsed_time(ev[i][j + 1]) for j in range(len(stages))] for i in range(K)])
 
 
-def kept_flop_count(mask_np, Lq: int, Lk: int, block: int, d: int) -> int:
-    """4 d x (valid query rows x valid keys) summed over the kept (query block, key block) pairs:
-    the two matrix products over kept blocks."""
+def kept_flop_count(mask_np, Lq: int, Lk: int, block: int, d: int, frame_tokens: int = 0) -> int:
+    """4 d x (query rows x keys each of them sees) summed over the kept (query block, key block)
+    pairs: the two matrix products over kept blocks.  With frame_tokens = F > 0 a row sees the chunk's
+    keys up to the end of its own frame; without, every valid key."""
     NQ, NK = mask_np.shape[-2], mask_np.shape[-1]
-    rows = np.minimum(np.arange(1, NQ + 1) * block, Lq) - np.arange(NQ) * block
-    keys = np.minimum(np.arange(1, NK + 1) * block, Lk) - np.arange(NK) * block
+    start = np.arange(NK, dtype=np.int64) * block
+    size = np.minimum(start + block, Lk) - start
+    row = np.arange(Lq, dtype=np.int64)
+    limit = np.minimum(Lk, Lk - Lq + (row // frame_tokens + 1) * frame_tokens) if frame_tokens > 0 else \
+        np.full(Lq, Lk, np.int64)
+    seen = np.add.reduceat(np.clip(limit[:, None] - start, 0, size), np.arange(NQ) * block, axis=0)
     kept = mask_np.reshape(-1, NQ, NK).astype(np.int64)
-    return int(4 * d * (kept * rows[:, None] * keys[None, :]).sum())
+    return int(4 * d * (kept * seen).sum())
 
 
 def cpu_baseline(wl, inp, mask_np, target_s: float):
@@ -183,11 +189,8 @@ def cpu_baseline(wl, inp, mask_np, target_s: float):
                 for i0 in range(0, wl.nq, 8):
                     rows = [(b, h, r) for r in range(i0, min(i0 + 8, wl.nq))]
                     O.attention_rows(inp["q"], inp["k"], inp["v"], mask_np, wl.block, rows, frame_tokens=F)
-                    for _, _, r in rows:
-                        lo, hi = r * wl.block, min((r + 1) * wl.block, wl.Lq)
-                        nk = sum(min((m + 1) * wl.block, wl.Lk) - m * wl.block for m in np.nonzero(mask_np[b, h, r])[0])
-                        flops += 4 * wl.d * (hi - lo) * nk
                     blocks += len(rows)
+                flops += kept_flop_count(mask_np[b:b + 1, h:h + 1], wl.Lq, wl.Lk, wl.block, wl.d, F)
                 heads += 1
                 if time.perf_counter() - t0 > target_s:
                     break
@@ -481,8 +484,8 @@ def main():
     t_att = t_plan + t_run_b + t_merge
 
     mask_np = mask.cpu().numpy()
-    kept_flops = float(kept_flop_count(mask_np, Lq, wl.Lk, wl.block, d))
-    dense_flops = 4.0 * B * H * Lq * wl.Lk * d
+    kept_flops = float(kept_flop_count(mask_np, Lq, wl.Lk, wl.block, d, F))
+    dense_flops = float(B * H * kept_flop_count(np.ones((1, NQ, NK), np.uint8), Lq, wl.Lk, wl.block, d, F))
     rho = kept_flops / dense_flops
 
     # dense baseline: the same attention steps over every key block

@@ -60,6 +60,21 @@ def test_kept_flop_count_matches_oracle(Lq, Lk, block):
     assert bench.kept_flop_count(mask, Lq, Lk, block, 128) == O.kept_flops(mask, Lq, Lk, block, 128)
 
 
+@pytest.mark.parametrize("Lq,Lk,block,F", [(256, 1024, 64, 64), (300, 1111, 128, 97), (200, 700, 64, 1),
+                                           (200, 700, 64, 500)])
+def test_kept_flop_count_frame_causal_counts_visible_keys(Lq, Lk, block, F):
+    # keys of later frames are not work: the oracle's visibility, row by row
+    rng = np.random.default_rng(F)
+    NQ, NK = -(-Lq // block), -(-Lk // block)
+    mask = (rng.random((1, 2, NQ, NK)) < 0.5).astype(np.uint8)
+    mask[..., (Lk - Lq) // block:] = 1
+    vis = np.stack([O.visible_keys(t, Lq, Lk, F) for t in range(Lq)])
+    kept = mask[0][:, np.arange(Lq) // block][:, :, np.arange(Lk) // block]          # [2, Lq, Lk]
+    want = 4 * 64 * int((kept * vis[None]).sum())
+    assert bench.kept_flop_count(mask, Lq, Lk, block, 64, F) == want
+    assert (want < O.kept_flops(mask, Lq, Lk, block, 64)) == (F < Lq)
+
+
 def test_kept_flop_count_3d_matches_oracle_sets():
     from paper_2605_31158_amd.workloads import WORKLOADS_3D
     wl = WORKLOADS_3D["tiny_3d"]
