@@ -319,40 +319,76 @@ def test_attn_schedule_invariants(case):
 
 
 CAUSAL = [
-    # B, H, Lq, Lk, d, block, F, label: frame edges on and off block and 64-key tile edges
-    (1, 2, 512, 1024, 128, 128, 128, "frames are blocks"),
-    (1, 2, 512, 1100, 64, 128, 64, "two frames a block, unaligned chunk"),
-    (1, 3, 700, 1533, 128, 64, 97, "frames cut blocks and tiles"),
-    (1, 1, 333, 800, 64, 128, 1, "one-token frames"),
-    (1, 2, 300, 700, 64, 64, 5000, "one frame longer than the chunk"),
+    # B, H, Lq, Lk, d, block, F, n_text, kvalid, lists, label: frame edges on and off block and 64-key
+    # tile edges; keys valid at the front of each block only; list entries in any order
+    (1, 2, 512, 1024, 128, 128, 128, 0, False, "ascending", "frames are blocks"),
+    (1, 2, 512, 1100, 64, 128, 64, 0, False, "ascending", "two frames a block, unaligned chunk"),
+    (1, 3, 700, 1533, 128, 64, 97, 0, False, "ascending", "frames cut blocks and tiles"),
+    (1, 1, 333, 800, 64, 128, 1, 0, False, "ascending", "one-token frames"),
+    (1, 2, 300, 700, 64, 64, 5000, 0, False, "ascending", "one frame longer than the chunk"),
+    (1, 2, 640, 1408, 128, 128, 160, 70, True, "ascending", "valid keys, text"),
+    (1, 2, 700, 1533, 64, 64, 97, 130, True, "shuffled", "valid keys, shuffled lists, text"),
+    (2, 1, 900, 2000, 128, 64, 300, 0, False, "shuffled", "shuffled lists"),
+    (1, 1, 1030 * 64 - 20, 1030 * 64 + 300, 64, 64, 9000, 0, False, "ascending", "past the grouping limit"),
 ]
 
 
-@pytest.mark.parametrize("case", CAUSAL, ids=[c[-1] for c in CAUSAL])
-def test_attn_frame_causal_walks_visible_tiles_only(case):
-    # tiles no row of a query block sees are not in the plan; results equal the oracle's
-    B, H, Lq, Lk, d, block, F, label = case
-    say(f"[causal] {label}: B={B} H={H} Lq={Lq} Lk={Lk} d={d} block={block} F={F}")
-    inp = make_clustered(B, H, Lq, Lk, d, block, F)
+def plan_case(case):
+    """Lists [B, H, NQ, NK] of a CAUSAL case: counts, idx, the mask they are, and the valid counts."""
+    B, H, Lq, Lk, d, block, F, n_text, with_valid, order, label = case
     rng = np.random.default_rng(Lq + F)
     NQ, NK = -(-Lq // block), -(-Lk // block)
     mask = (rng.uniform(size=(B, H, NQ, NK)) < 0.5).astype(np.uint8)
     mask[..., (Lk - Lq) // block:] = 1
+    if NQ > 1024:                               # few blocks each, so that the oracle is quick
+        mask &= (rng.uniform(size=mask.shape) < 0.02).astype(np.uint8)
+        mask[..., -1] = 1
+    kv = rng.integers(0, block + 1, size=NK).astype(np.int32) if with_valid else None
+    counts = mask.sum(-1).astype(np.int32)
+    idx = np.full(mask.shape, -7, np.int32)
+    for ix in np.ndindex(B, H, NQ):
+        ent = np.nonzero(mask[ix])[0]
+        idx[ix][:ent.size] = rng.permutation(ent) if order == "shuffled" else ent
+    return counts, idx, mask, kv
+
+
+@pytest.mark.parametrize("case", CAUSAL, ids=[c[-1] for c in CAUSAL])
+def test_attn_frame_causal_walks_visible_tiles_only(case):
+    # every unit of the plan walks the tiles that some row of it keeps and sees, and no other; results
+    # equal the oracle's
+    B, H, Lq, Lk, d, block, F, n_text, with_valid, order, label = case
+    say(f"[causal] {label}: B={B} H={H} Lq={Lq} Lk={Lk} d={d} block={block} F={F} n_text={n_text}")
+    inp = make_clustered(B, H, Lq, Lk, d, block, F)
+    counts, idx, mask, kv = plan_case(case)
     g = to_gpu(inp)
-    counts, idx = la.mask_to_list(torch.from_numpy(mask).cuda(), block, Lq, Lk, d)
-    shape = la.make_shape(B, H, Lq, Lk, d, block, 0, F)
+    shape = la.make_shape(B, H, Lq, Lk, d, block, n_text, F)
     ws = torch.empty(la.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
-    o, lse = la.sparse_attn_fwd(g["q"], g["k"], g["v"], counts, idx, block, frame_tokens=F, want_lse=True, ws=ws)
+    o, lse = la.sparse_attn_fwd(g["q"], g["k"], g["v"], torch.from_numpy(counts).cuda(), torch.from_numpy(idx).cuda(),
+                                block, n_text=n_text, frame_tokens=F, want_lse=True, ws=ws,
+                                kvalid=None if kv is None else torch.from_numpy(kv).cuda())
     s = la.plan_schedule(shape, ws)
-    o_ref, lse_ref = O.attention(inp["q"], inp["k"], inp["v"], mask, block, frame_tokens=F)
-    compare(bf16_tensor_to_f64(o), lse.cpu().numpy().astype(np.float64), o_ref, lse_ref, label)
-    # visible tiles of each query block's own list: those before its last row's last visible key
-    last = np.minimum(Lq, (np.arange(NQ) + 1) * block) - 1
-    lim = np.minimum(Lk, Lk - Lq + (last // F + 1) * F)
-    key0 = np.arange(0, Lk, 64)
-    own = mask[..., key0 // block].astype(np.int64) * (key0[None, :] < lim[:, None])
-    rt = own.sum(-1).reshape(B * H, NQ)
-    check_schedule(s, row_tiles=rt)
+    check_schedule(s)
+    lists = (counts, idx, block, Lq, Lk, n_text, F, kv)
+    want = unit_tiles(*lists)
+    np.testing.assert_array_equal(s["ucount"], want.reshape(-1))
+    # frames shorter than the chunk hide tiles from every plan of these cases
+    whole = int(unit_tiles(*lists, order="natural" if mask.shape[2] > 1024 else "key", visible=False).sum())
+    assert (int(want.sum()) < whole) == (F < Lq) and (F < Lq or int(want.sum()) == whole)
+    # the oracle over the valid keys of the kept blocks that a row sees
+    o, lse = bf16_tensor_to_f64(o), lse.cpu().numpy().astype(np.float64)
+    NQ, NK = mask.shape[2:]
+    picked = range(NQ) if NQ <= 64 else [0, 1, 139, 140, 141, 281, 282, 777, 1023, 1024, NQ - 1]
+    valid = np.minimum(block, Lk - block * np.arange(NK)) if kv is None else \
+        np.minimum(kv, Lk - block * np.arange(NK))
+    alive = (np.arange(Lk) % block) < valid[np.arange(Lk) // block]
+    for b, h in np.ndindex(B, H):
+        x = {n: O.bf16_bits_to_f64(inp[n][b, h]) for n in "qkv"}
+        for i in picked:
+            rows = np.arange(i * block, min(Lq, (i + 1) * block))
+            cand = np.nonzero((mask[b, h, i][np.arange(Lk) // block] != 0) & alive)[0]
+            ok = np.array([O.visible_keys(t, Lq, Lk, F)[cand] for t in rows])
+            ob, lb = O.attention_block(x["q"][rows], x["k"][cand], x["v"][cand], ok, 1.0 / math.sqrt(d))
+            compare(o[b, h, rows], lse[b, h, rows], ob, lb, f"{label} {(b, h, i)}")
 
 
 @pytest.mark.parametrize("d", [64, 128])
