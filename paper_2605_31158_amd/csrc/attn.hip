@@ -338,40 +338,56 @@ __device__ __forceinline__ float row_max(float x) {
 }
 
 // Softmax of one tile with a lazily raised running max (base 2).  P is first formed against the
-// current max m_run, which is left alone while every lane's sum of its values of a row stays
-// within 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise the row
-// max of the tile is taken, m_run raised to it, O and l rescaled, and P formed again.  Most tiles
-// thus skip both the row max and the rescale.  On the first tile of a piece m_run is -inf: the first
-// pass then gives inf or NaN sums, which fail the test too.
+// current max m_run, which is left alone while every sum of a row's values over half of the tile's
+// keys stays within 2^8 (so no value exceeds 2^8 and the O accumulators keep their range); otherwise
+// the row max of the tile is taken, m_run raised to it, O and l rescaled, and P formed again.  Most
+// tiles thus skip both the row max and the rescale.  On the first tile of a piece m_run is -inf: the
+// first pass then gives inf or NaN sums, which fail the test too.
+// A raised max makes the largest P exactly 1, with no rounding to bf16, so the limit matters to the
+// precision: with 2^8 over a lane's 16 values alone (d = 128) the error against 64 bits was up to
+// 0.15 % larger, 0.0023393 instead of 0.0023358 at 720P.  A lane tests its own values first, at half
+// the limit where it holds a quarter of the keys; the sums of the halves are taken where that fails
+// (in every tile they cost 2 % of the call).
 template <int D>
 __device__ __forceinline__ void softmax_tile(typename Mma<D>::Acc (*sacc)[Mma<D>::QT], bf16x8 (*pb)[Mma<D>::QT],
                                              typename Mma<D>::Acc (*oacc)[Mma<D>::QT], float* m_run, float* l_run,
                                              float scale_log2) {
   using X = Mma<D>;
   float rs[X::QT];
-  bool redo = false;
+  bool over = false;
 #pragma unroll
   for (int qt = 0; qt < X::QT; ++qt) {
     rs[qt] = softmax_exp<D>(sacc, pb, qt, m_run[qt], scale_log2);
-    redo = redo || !(rs[qt] <= 256.f);
+    over = over || !(rs[qt] <= (X::NG == 4 ? 128.f : 256.f));
   }
-  if (__builtin_expect(__any(redo), 0)) {
+  if (__builtin_expect(__any(over), 0)) {
+    if constexpr (X::NG == 4) {
+      over = false;
 #pragma unroll
-    for (int qt = 0; qt < X::QT; ++qt) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < KT / X::MR; ++kt)
-#pragma unroll
-        for (int i = 0; i < X::AR; ++i) mx = fmaxf(mx, sacc[kt][qt][i]);
-      const float mt = row_max<D>(mx) * scale_log2;
-      if (mt > m_run[qt]) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - mt);   // 0 while m_run is -inf
-        m_run[qt] = mt;
-        l_run[qt] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < D / X::MR; ++dt) oacc[dt][qt] *= alpha;
+      for (int qt = 0; qt < X::QT; ++qt) {
+        const uint32_t r = __builtin_bit_cast(uint32_t, rs[qt]);
+        const auto h = __builtin_amdgcn_permlane32_swap(r, r, false, false);      // lanes l and l ^ 32
+        over = over || !(__builtin_bit_cast(float, (uint32_t)h[0]) + __builtin_bit_cast(float, (uint32_t)h[1]) <= 256.f);
       }
-      rs[qt] = softmax_exp<D>(sacc, pb, qt, m_run[qt] == -INFINITY ? 0.f : m_run[qt], scale_log2);
+    }
+    if (X::NG == 2 || __any(over)) {
+#pragma unroll
+      for (int qt = 0; qt < X::QT; ++qt) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < KT / X::MR; ++kt)
+#pragma unroll
+          for (int i = 0; i < X::AR; ++i) mx = fmaxf(mx, sacc[kt][qt][i]);
+        const float mt = row_max<D>(mx) * scale_log2;
+        if (mt > m_run[qt]) {
+          const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - mt);   // 0 while m_run is -inf
+          m_run[qt] = mt;
+          l_run[qt] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < D / X::MR; ++dt) oacc[dt][qt] *= alpha;
+        }
+        rs[qt] = softmax_exp<D>(sacc, pb, qt, m_run[qt] == -INFINITY ? 0.f : m_run[qt], scale_log2);
+      }
     }
   }
 #pragma unroll

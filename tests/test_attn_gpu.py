@@ -470,3 +470,29 @@ def test_attn_frame_causal_order_of_query_blocks(case):
     by_key, by_frame = (int(unit_tiles(*lists, order=x).sum()) for x in ("key", "frames"))
     assert total <= int(unit_tiles(*lists, order="key", visible=False).sum())
     assert total == (by_key if keep > 1 else by_frame) == min(by_key, by_frame), (total, by_key, by_frame)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_attn_running_max_is_raised_over_half_a_tile(d):
+    # Two keys of one half of the second tile have weight 128.49 over the first tile's, 256.98 together:
+    # past 2^8, so the running max is raised, both weights are exactly 1 and V = 1 gives exactly 1.
+    # Left at the first tile's max they round to 128 in bf16, and the output to 0.99609375
+    B, H, Lq, Lk = 1, 2, 64, 128
+    q = torch.zeros((B, H, Lq, d), dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros((B, H, Lk, d), dtype=torch.bfloat16, device="cuda")
+    v = torch.ones_like(k)
+    q[..., 0] = 1
+    k[:, :, 64:, 0] = -64                      # weight 0
+    k[:, :, [64, 72], 0] = 1
+    mask = torch.ones((B, H, 1, 2), dtype=torch.uint8, device="cuda")
+    counts, idx = la.mask_to_list(mask, 64, Lq, Lk, d)
+    scale = math.log(128.49)
+    # enough units that one workgroup walks both tiles of a unit: 256 units of two tiles
+    reps = (1, 128, 1, 1)
+    q, k, v = q.repeat(reps), k.repeat(reps), v.repeat(reps)
+    counts, idx = counts.repeat(1, 128, 1), idx.repeat(reps)
+    o, lse = la.sparse_attn_fwd(q, k, v, counts, idx, 64, scale=scale, want_lse=True)
+    torch.cuda.synchronize()
+    assert bool((o == 1).all()), o.float().min()
+    want = math.log(64 + 2 * 128.49)
+    assert float((lse - want).abs().max()) <= LSE_TOL
