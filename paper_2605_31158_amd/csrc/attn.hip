@@ -40,14 +40,14 @@
 // exponentials, 8 cycles each) and what the tile's record, masks and loads need.  Records, masks
 // and load addresses are therefore kept to about 40 scalar instructions (150 and a 9th load in
 // four of the waves, with all loads on group 1: 27 % more cycles).  Measured with every block kept
-// (16 heads, 6240 x 43680, d 128): 2059 -> 1861 us, on zeros 1608 -> 1263 us (1.77 PFLOP/s): on
-// real data the kernel is bound by the card's power, not by its cycles (a large bf16 matrix product
-// reaches 1.39 PFLOP/s on random data and 1.80 on zeros).
+// (16 heads, 6240 x 43680, d 128, with 32x32x16 MFMAs, one box): 2039 -> 1844 us, on zeros 1607 ->
+// 1271 us (1.76 PFLOP/s): on real data the kernel is bound by the card's power, not by its cycles (a
+// large bf16 matrix product reaches 1.39 PFLOP/s on random data and 1.80 on zeros).
 //
 // Per wave and 64-key tile:
 //   S^T (64 keys x 32 queries) = K_tile (64 x d) . Q^T        MFMA, bf16 in, fp32 out
-//   online softmax over keys (fp32, base 2; the running max is only raised when a tile's
-//   max exceeds it by more than 2^8, so most tiles skip the rescale of O)
+//   online softmax over keys (fp32, base 2; the running max is only raised when weights over it
+//   pass 2^8, so most tiles skip the rescale of O)
 //   O^T (d x 32) += V^T (d x 64) . P^T (64 x 32)              MFMA
 // S^T is computed transposed so that its accumulator layout is, 8 values at a time, directly the B
 // operand of the P.V product.  The V^T operand is read with the LDS transpose load
@@ -55,7 +55,7 @@
 // d = 64.  On random operands the card sustains 2040 TFLOP/s of the first and 1725 of the second
 // (power), but the first holds up the vector instructions of the other wave more (the softmax of a
 // tile takes 1049 cycles beside it, 718 beside the second, 623 alone).  With d = 128 the power
-// decides: 720P 2128 -> 2031 us, 480P dense 1855 -> 1736 us for the whole attention call; with d = 64
+// decides: 720P step 2283 -> 2205 us, 480P dense 1844 -> 1786 us (on zeros 1271 -> 1365); with d = 64
 // a tile has the same softmax for half the products, and 16x16x32 was 2-3 % slower.
 #include <math.h>
 
@@ -445,7 +445,8 @@ __device__ inline int block_key_limit(int qb, int Lq, int Lk, int block, int F, 
 // With frames inside the chunk a list owns a sub-tile only when some row of its query block sees
 // it (block_key_limit).  The frames a query block cannot see are the later part of the chunk, 3/8
 // of it with four frames, and a fully masked tile takes as long as a visible one: 24 heads, 14400
-// queries in four frames, 117 of 563 blocks of 128 kept: 2597 -> 1752 us for the whole call.
+// queries in four frames, 117 of 563 blocks of 128 kept: 329508 -> 222102 tiles, 2658 -> 1777 us for
+// the whole call with the attention loop of the time (1540 with the present one on the same box).
 // The grouping key of a query block is its entry h0 (the first past the text blocks of an ascending
 // list, as the selection writes them), or the first entry past the text blocks when entry h0 is
 // none, when that is historical (below h1), NK otherwise.  Any other list order only changes the

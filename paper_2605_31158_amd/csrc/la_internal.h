@@ -90,9 +90,9 @@ int device_cu_count();
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // ---------------------------------------------------------------------------
-// Wave-wide sums and scans with DPP row operations, row broadcasts and the row-pair / half-wave
-// swaps: no LDS round trip.  (With __shfl every step is one or two ds_bpermute, over 100 cycles
-// each in a chain; a scan of the selection's 64-bit weights has twelve of them.)
+// Wave-wide sums and scans with DPP row shifts and row broadcasts: no LDS round trip.  (With __shfl
+// every step is one or two ds_bpermute, over 100 cycles each in a chain; a scan of the selection's
+// 64-bit weights has twelve of them.)
 
 // x of the lane that `ctrl` names, 0 where there is none or its row is not in row_mask
 template <int ctrl, int row_mask>

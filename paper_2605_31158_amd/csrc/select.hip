@@ -465,11 +465,16 @@ inline int score_group(const Dims& dm) {
 }
 
 // Whether the workgroups that score a head pool its queries themselves (each all of them) instead
-// of a launch of pool_q before.  For the smallest calls, up to eight query blocks read by few
-// workgroups: there the launch costs more than the reads (the selection of 2 heads, 4 query blocks
-// and 12 candidates 9.7 -> 8.5 us, of 8 heads, 8 and 32: 11.2 -> 9.8), 0 to 2 us over eleven shapes up
-// to 256 such reads and a launch less for the host.  Past that the reads add up: even at 720 (12.2
-// and 12.2 us), slower beyond (20 heads, 1 query block, 312 candidates of 128: 42.9 -> 48.9 us).
+// of a launch of pool_q before.  For the smallest calls, up to eight query blocks (one a wave) read
+// by few workgroups: there the launch costs more than the reads.  With it and without it in turn, us
+// for the selection, up to 256 block reads in all (9 shapes, both block sizes and head dimensions):
+// 4 to 30 % less with it (2 heads, 4 query blocks, 12 candidates of 64 x 64: 9.8 -> 8.0; 8 heads, 8
+// and 32 of 128 x 128: 14.3 -> 13.3).  Beyond, it depends on the workgroups: with at most one a CU it
+// is still 1 to 17 % less at 384 to 1024 reads (8 heads, 8, 64: 16.7 -> 15.8), with more than one 5
+// to 16 % more from 512 reads on (16 heads, 1, 256: 31.1 -> 33.2; 20 heads, 1, 312: 41.8 -> 47.5; not
+// with blocks of 64 x 64: 13.6 -> 12.1).  Up to 256 reads there is at most one a CU.  More than eight
+// query blocks are pooled one after another by a wave: 16 blocks 0.94 to 1.12, 32 blocks 1.12 to 1.38
+// times the time at 256 and 512 reads.
 inline bool fold_pool_q(const Dims& dm, int G) {
   return dm.NQ <= 8 && (int64_t)ceil_div(dm.M, G) * dm.BH * dm.NQ <= 256;
 }
