@@ -193,6 +193,12 @@ struct Geom {
   int BH, U;          // heads and units of the plan (bounds for the fields read from it)
 };
 
+// Frame-causal chunks (F > 0): first key that query row t does not see, the end of its chunk frame.
+// (One 32-bit division; with 64-bit ones the planner took 0.1 to 0.2 us more.)
+__device__ __forceinline__ int row_key_limit(int t, int Lk, int F, int chunk0) {
+  return (int)min((int64_t)Lk, (int64_t)chunk0 + (int64_t)((uint32_t)t / (uint32_t)F + 1u) * F);
+}
+
 // Per-wave constants of the tile loop (klimit changes with the unit).
 struct WaveCtx {
   int klimit[2];             // keys >= klimit[qt] are invisible to this lane's query row of column qt
@@ -436,8 +442,7 @@ __device__ inline int block_subtiles(int j, int Lk, int block, const int32_t* __
 // there on belong to frames later than the block's last row's.
 __device__ inline int block_key_limit(int qb, int Lq, int Lk, int block, int F, int chunk0) {
   if (F <= 0) return Lk;
-  const int last = min(Lq, (qb + 1) * block) - 1;
-  return (int)min((int64_t)Lk, (int64_t)chunk0 + ((int64_t)last / F + 1) * F);
+  return row_key_limit(min(Lq, (qb + 1) * block) - 1, Lk, F, chunk0);
 }
 
 // One workgroup per unit: its query blocks (rank by (key, block index) inside the head) and the
@@ -472,7 +477,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   extern __shared__ __align__(16) uint32_t own[];     // 4 ownership bits per key block
   __shared__ int sh[kPlanThreads / 64];
   __shared__ int qsel[4];
-  __shared__ int slim[4];             // block_key_limit of the unit's query blocks
+  __shared__ int4 slim;               // block_key_limit of the unit's query blocks
   __shared__ __attribute__((aligned(16))) uint64_t skey[kMaxGroupNQ + 2];
   __shared__ int rank[kMaxGroupNQ];
   const int u = blockIdx.x;
@@ -484,7 +489,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   for (int i = tid; i < nwords; i += kPlanThreads) own[i] = 0;
   if (tid < 4) qsel[tid] = -1;
   const bool grouped = NQ <= kMaxGroupNQ;
-  int nhist = 0;                      // historical entries of this thread's lists (frames only)
+  const bool choose = grouped && F > 0 && F < Lq && NQ > NL;      // the order makes a difference
+  int nhist = 0;                      // historical entries of this thread's lists (if choose)
   if (grouped)
     for (int i = tid; i < NQ; i += kPlanThreads) {
       const size_t row = (size_t)bh * NQ + i;
@@ -508,7 +514,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
       const int lim = F > 0 ? ceil_div(block_key_limit(i, Lq, Lk, block, F, chunk0), block) : 0;
       skey[i] = ((uint64_t)lim << 32) | ((uint64_t)key << 16) | (uint64_t)i;
       rank[i] = 0;
-      if (F > 0) {
+      if (choose) {
         // of an ascending list that keeps the whole chunk, what lies before it, less the text blocks
         // when it keeps them; of any other list, all entries (more than there may be)
         const int tail = NK - h1;
@@ -518,7 +524,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
       }
     }
   if (grouped && tid < 2) skey[NQ + tid] = ~0ull;      // padding of the pairs read below
-  if (grouped && F > 0) {
+  if (choose) {
     int hist;
     block_excl_scan_i(nhist, sh, &hist);
     const int64_t frames = ceil_div(Lq, F);
@@ -559,7 +565,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
   __syncthreads();
   if (tid < NL) {
     qmap[(size_t)u * NL + tid] = qsel[tid];
-    slim[tid] = block_key_limit(max(qsel[tid], 0), Lq, Lk, block, F, chunk0);
+    if (F > 0) ((int*)&slim)[tid] = block_key_limit(max(qsel[tid], 0), Lq, Lk, block, F, chunk0);
   }
   // all lists of the unit at once, kPlanThreads / NL threads each (one after another, every list
   // cost two more dependent loads; with the ranking above 10.4 -> 9.1 us at 400 units of four lists)
@@ -577,44 +583,49 @@ __global__ __launch_bounds__(kPlanThreads) void plan_union_kernel(const int32_t*
     }
   }
   __syncthreads();
-  // the lists of `bits` that see the 64 keys from key0 on
-  auto seen = [&](uint32_t bits, int key0) {
-    if (F > 0)
-      for (int L = 0; L < NL; ++L)
-        if (key0 >= slim[L]) bits &= ~(1u << L);
-    return bits;
+  const int4 lim4 = slim;
+  // the ownership bits of word wi (8 key blocks) whose lists see sub-tile `sub` of their block: with
+  // frames, list L sees the first ones of the word (every sub-tile tested against every limit in LDS:
+  // 15.3 instead of 10.8 us of planning for 16 heads, 64 queries, 4096 keys in blocks of 128, and of 10
+  // without frames)
+  auto seen = [&](uint32_t x, int wi, int sub) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int L = 0; L < 4; ++L) {
+      const int lim = L == 0 ? lim4.x : L == 1 ? lim4.y : L == 2 ? lim4.z : lim4.w;
+      const int nv = min(max(lim - 8 * wi * block, 0), 8 * block);            // keys of the word it sees
+      const int nb = ((nv + KT - 1) / KT - sub + nsub - 1) >> (nsub - 1);     // blocks
+      m |= (nb >= 8 ? ~0u : (1u << (4 * nb)) - 1) & (0x11111111u << L);
+    }
+    return x & m;
   };
   const int per = (nwords + kPlanThreads - 1) / kPlanThreads;
   const int w0 = min(tid * per, nwords), w1 = min(w0 + per, nwords);
-  int cnt = 0;
-  for (int wi = w0; wi < w1; ++wi) {
-    const uint32_t x = own[wi];
+  // f(key block, sub-tile, owning lists) for every sub-tile of this thread's words
+  auto subtiles = [&](auto f) {
+    for (int wi = w0; wi < w1; ++wi) {
+      const uint32_t x = own[wi];
+      if (!x) continue;
+      const uint32_t x0 = F > 0 ? seen(x, wi, 0) : x, x1 = F > 0 && nsub > 1 ? seen(x, wi, 1) : x;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t bits = (x >> (4 * e)) & 15u;
-      if (!bits) continue;
-      const int j = 8 * wi + e;
-      const int ns = block_subtiles(j, Lk, block, kvalid);
-      for (int sub = 0; sub < ns; ++sub) cnt += seen(bits, j * block + sub * KT) != 0;
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t b0 = (x0 >> (4 * e)) & 15u, b1 = (x1 >> (4 * e)) & 15u;
+        if (!b0) continue;                       // the first sub-tile is seen if the second is
+        const int j = 8 * wi + e;
+        const int ns = block_subtiles(j, Lk, block, kvalid);
+        if (ns > 0) f(j, 0, b0);
+        if (ns > 1 && b1) f(j, 1, b1);
+      }
     }
-  }
+  };
+  int cnt = 0;
+  auto count = [&](int, int, uint32_t) { ++cnt; };
+  subtiles(count);
   int total;
   int pos = block_excl_scan_i(cnt, sh, &total);
   int32_t* out = ulist + (size_t)u * NK * nsub;
-  for (int wi = w0; wi < w1; ++wi) {
-    const uint32_t x = own[wi];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t bits = (x >> (4 * e)) & 15u;
-      if (!bits) continue;
-      const int j = 8 * wi + e;
-      const int ns = block_subtiles(j, Lk, block, kvalid);
-      for (int sub = 0; sub < ns; ++sub) {
-        const uint32_t b = seen(bits, j * block + sub * KT);
-        if (b) out[pos++] = (j << 5) | (sub << 4) | (int)b;
-      }
-    }
-  }
+  auto emit = [&](int j, int sub, uint32_t b) { out[pos++] = (j << 5) | (sub << 4) | (int)b; };
+  subtiles(emit);
   if (tid == 0) ucount[u] = total;
 }
 
@@ -749,7 +760,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tiles_kernel(const int32_t*
   if (F > 0)
     for (int L = 0; L < QR / block; ++L) {
       const int qb = qmap[(size_t)u * (QR / block) + L];
-      if (qb >= 0) maskfrom = (int)min((int64_t)maskfrom, (int64_t)chunk0 + ((int64_t)qb * block / F + 1) * F);
+      if (qb >= 0) maskfrom = min(maskfrom, row_key_limit(qb * block, Lk, F, chunk0));
     }
   const int32_t* ul = ulist + (size_t)u * NK * nsub;
   for (int a = tid; a < n; a += kPlanThreads) {
@@ -869,8 +880,7 @@ __device__ __forceinline__ void start_piece(WaveState<D>& st, WaveCtx& w, const 
     // Key n is visible to query row t when n < Lk and, with frames of F tokens inside the chunk,
     // when its chunk frame is not later than t's: n < chunk0 + (t / F + 1) F (context keys,
     // n < chunk0, always pass).  One limit per lane and row replaces per-key frame arithmetic.
-    const int64_t lim = gm.F > 0 ? (int64_t)gm.chunk0 + ((int64_t)row / gm.F + 1) * gm.F : (int64_t)gm.Lk;
-    w.klimit[qt] = (int)(lim < gm.Lk ? lim : gm.Lk);
+    w.klimit[qt] = gm.F > 0 ? row_key_limit(row, gm.Lk, gm.F, gm.chunk0) : gm.Lk;
   }
   // complete the Q loads here: left pending, they would make every later Q.K^T (reached also
   // without a piece start) wait for all vector memory traffic, the tile loads in flight included
