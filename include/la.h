@@ -148,7 +148,8 @@ la_status la_sparse_attn_fwd(const la_shape* shape, const void* q, const void* k
 /* la_sparse_attn_fwd in its three steps, for callers that time or reuse them.
  * The work plan depends only on the lists: units of 256 query rows (query blocks of a
  * head grouped by the first historical entry of their lists, the first kept historical
- * block for the ascending lists the selection writes; any order gives the same results),
+ * block for the ascending lists the selection writes, in frame-causal calls behind their
+ * frame where that leaves fewer tiles; any order gives the same results),
  * the union of their lists as
  * 64-key tiles, and the split of the work over one persistent workgroup per CU of the
  * current device: whole units in rounds (the workgroups of one XCD start consecutive

@@ -3,10 +3,10 @@
 //
 // Work decomposition
 //   * A unit is 256 query rows of one (batch, head): four query blocks of 64 rows or two of 128.
-//     Query blocks are grouped by the first historical key block they keep, so that blocks
-//     which chose the same context share a unit.  Its tiles are the 64-key sub-tiles of the
-//     union of its blocks' kept lists, in ascending key order, each tagged with which of the
-//     unit's blocks kept it.
+//     Query blocks are grouped by the first historical key block they keep (frame-causal calls may
+//     put their frame before it, see plan_union_kernel), so that blocks which chose the same
+//     context share a unit.  Its tiles are the 64-key sub-tiles of the union of its blocks' kept
+//     lists, in ascending key order, each tagged with which of the unit's blocks kept it.
 //   * A planner (two or three small kernels) computes the grouping, every unit's union list, the
 //     schedule and one record per tile (first key, head, unit, ownership) in the tile sequence.
 //     One persistent workgroup per CU runs, first, whole units handed out in rounds: in each
