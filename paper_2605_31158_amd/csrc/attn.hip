@@ -40,7 +40,7 @@
 // exponentials, 8 cycles each) and what the tile's record, masks and loads need.  Records, masks
 // and load addresses are therefore kept to about 40 scalar instructions (150 and a 9th load in
 // four of the waves, with all loads on group 1: 27 % more cycles).  Measured with every block kept
-// (16 heads, 6240 x 43680, d 128, with 32x32x16 MFMAs, one box): 2039 -> 1844 us, on zeros 1607 ->
+// (16 heads, 6240 x 43680, d 128, with 32x32x16 MFMAs, one card): 2039 -> 1844 us, on zeros 1607 ->
 // 1271 us (1.76 PFLOP/s): on real data the kernel is bound by the card's power, not by its cycles (a
 // large bf16 matrix product reaches 1.39 PFLOP/s on random data and 1.80 on zeros).
 //
@@ -451,7 +451,7 @@ __device__ inline int block_key_limit(int qb, int Lq, int Lk, int block, int F, 
 // it (block_key_limit).  The frames a query block cannot see are the later part of the chunk, 3/8
 // of it with four frames, and a fully masked tile takes as long as a visible one: 24 heads, 14400
 // queries in four frames, 117 of 563 blocks of 128 kept: 329508 -> 222102 tiles, 2658 -> 1777 us for
-// the whole call with the attention loop of the time (1540 with the present one on the same box).
+// the whole call with the attention loop of the time (1540 with the present one on the same card).
 // The grouping key of a query block is its entry h0 (the first past the text blocks of an ascending
 // list, as the selection writes them), or the first entry past the text blocks when entry h0 is
 // none, when that is historical (below h1), NK otherwise.  Any other list order only changes the
